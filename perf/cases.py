@@ -1,0 +1,627 @@
+"""Performance cases: what users of the solver and of its warm-start network run.
+
+A case is a plain dict; `prepare` builds what a user's program holds before the
+call (media, boundary conditions, start fields, the network), `run` is one
+pass through the public entry points.  Sizes are those of the repository's
+workloads: the 256^3 throughput cell, 128^3 solves, the parametric sweep's and
+the training sets' batches, the paper's unit cells, the smoke check's 16^3
+cell, and ragged extents as the parity tests use them.  A steady solve repeats
+the same block of steps thousands of times; a pass here is the first few
+hundred steps, with the observables checked on the way as in a full solve.
+"""
+
+from __future__ import annotations
+
+import math
+import os
+import types
+
+import numpy as np
+import torch
+
+from paper_1503_08718_amd import solver
+from paper_1503_08718_amd import warmstart as ws
+
+DEV = "cuda:0"
+PKG = os.path.dirname(os.path.abspath(ws.__file__))
+TUNED = os.path.join(PKG, "tuned_launch.txt")
+MODEL = os.path.join(PKG, "warmstart_model.pt")
+OBSERVED = ("keff", "keff_hot", "keff_cold", "keff_vol", "temp_mean")
+
+
+# ---------------------------------------------------------------------------
+# cases
+# ---------------------------------------------------------------------------
+
+
+def _solve(name, n, prec="f32", storage="moments", axis=0, sides="periodic", start="smooth", steps=400):
+    c = dict(kind="solve", nx=n[0], ny=n[1], nz=n[2], prec=prec, storage=storage, axis=axis, sides=sides, start=start,
+             steps=steps)
+    return dict(c, name=name) if name else c
+
+
+def listed():
+    return [
+        # the throughput benchmark: one large cell in FP32 moment storage
+        _solve("solve_f32_256", (256, 256, 256)),
+        # k_L of a 128^3 cell (z gradient, adiabatic sides)
+        _solve("solve_f32_128", (128, 128, 128), axis=2, sides="adiabatic"),
+        # the FP64 reference that FP32 results are judged against
+        _solve("solve_f64_128", (128, 128, 128), prec="f64"),
+        # ragged extents: no two nodes of a row share an aligned vector
+        _solve("solve_f32_ragged", (75, 61, 87), axis=1, sides="adiabatic"),
+        # population storage, the one a medium starts in
+        _solve("solve_populations_96", (96, 96, 96), storage="populations"),
+        # the smallest call: the smoke check's cell, where launches are all
+        _solve("solve_f64_16", (16, 16, 16), prec="f64", storage="populations", start="zero"),
+        # the parametric sweep: x and z solves of cells of uneven size in one batch, its shape tuned first
+        dict(name="batch_sweep", kind="batch", cells=12, nxy=0, sizes="64,96,128", tune=True, start="smooth", steps=400),
+        # training fields of the warm-start network: x and z solves of small cells
+        dict(name="batch_training_fields", kind="batch", cells=16, nxy=0, sizes="32,40,48,64", tune=False,
+             start="linear", steps=400),
+        # the paper's unit cells over braiding angle and fibre fraction
+        dict(name="batch_unit_cells", kind="batch", cells=9, nxy=56, sizes="", tune=False, start="zero", steps=400),
+        # reading a solve's answer: k_eff, temperature and flux fields
+        dict(name="observe_f32_128", kind="observe", nx=128, ny=128, nz=128, prec="f32", storage="moments"),
+        # serving a start field: one inference of the trained network for a 128^3 cell
+        dict(name="predict_128", kind="predict", nx=128, ny=128, nz=128),
+        # one training iteration: forward, loss, gradients, Adam, batch 4 of 64^3 cells
+        dict(name="train_64", kind="train", nx=64, ny=64, nz=64, batch=4),
+    ]
+
+
+def _extent(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    kind = rng.choice(["solve", "solve", "solve", "solve", "batch", "batch", "observe", "predict", "train"])
+    if kind == "solve":
+        # single cells from 16^3 to 192^3, mostly even extents, some odd
+        n = []
+        for _ in range(3):
+            e = _extent(rng, 16, 192)
+            n.append(e if rng.random() < 0.3 else max(16, e // 8 * 8))
+        prec = rng.choice(["f32", "f32", "f64"])
+        storage = rng.choice(["moments", "moments", "populations"])
+        return _solve("", n, prec, storage, rng.choice([0, 1, 2]), rng.choice(["periodic", "adiabatic"]),
+                      rng.choice(["smooth", "zero"]))
+    if kind == "batch":
+        if rng.random() < 0.25:
+            return dict(kind="batch", cells=rng.randint(2, 9), nxy=rng.choice([32, 40, 48, 56, 64]), sizes="",
+                        tune=False, start="zero", steps=400)
+        big = rng.random() < 0.4
+        return dict(kind="batch", cells=rng.randint(2, 10 if big else 16), nxy=0,
+                    sizes="64,96,128" if big else rng.choice(["32,40,48,64", "24,30,45,64"]), tune=rng.random() < 0.3,
+                    start=rng.choice(["linear", "smooth"]), steps=400)
+    if kind == "observe":
+        return dict(kind="observe", nx=_extent(rng, 16, 192), ny=_extent(rng, 16, 192), nz=_extent(rng, 16, 192),
+                    prec=rng.choice(["f32", "f32", "f64"]), storage=rng.choice(["moments", "moments", "populations"]))
+    if kind == "predict":
+        return dict(kind="predict", nx=_extent(rng, 32, 192), ny=_extent(rng, 32, 192), nz=_extent(rng, 32, 192))
+    s = (32, 40, 48, 64)
+    return dict(kind="train", nx=rng.choice(s), ny=rng.choice(s), nz=rng.choice(s), batch=rng.choice([1, 2, 3, 4]))
+
+
+# ---------------------------------------------------------------------------
+# media and start fields
+# ---------------------------------------------------------------------------
+
+
+def _braid(nx, ny, nz, gamma_deg, v, ka=10.0, kt=1.0, km=0.2):
+    """Four-directional braided cell on the GPU: (phase uint8 [nz][ny][nx], k
+    [5][6]); straight elliptical yarns along the four family axes, periodic."""
+    g = math.radians(gamma_deg)
+    sg, cg = math.sin(g) / math.sqrt(2.0), math.cos(g)
+    aspect = math.sqrt(3.0) * cg
+    axes = np.array([[sx * sg, sy * sg, cg] for sx, sy in ((1, 1), (-1, 1), (1, -1), (-1, -1))])
+    x = (torch.arange(nx, device=DEV, dtype=torch.float32) + 0.5).view(1, 1, nx)
+    y = (torch.arange(ny, device=DEV, dtype=torch.float32) + 0.5).view(1, ny, 1)
+    z = (torch.arange(nz, device=DEV, dtype=torch.float32) + 0.5).view(nz, 1, 1)
+    best = torch.full((nz, ny, nx), float("inf"), device=DEV)
+    fam_of = torch.zeros((nz, ny, nx), dtype=torch.uint8, device=DEV)
+    ext = (nx, ny, nz)
+    for fam, u in enumerate(axes):
+        n = np.cross([0.0, 0.0, 1.0], u)
+        n /= np.linalg.norm(n)
+        m = np.cross(u, n)
+        for line in range(2):
+            anchor = ((line / 2 + fam / 8 + 0.25) * nx, (line / 2 + 0.25) * ny, nz / 2.0)
+            offs = set()
+            for s in ((i, j, k) for i in (-1, 0, 1) for j in (-1, 0, 1) for k in (-1, 0, 1)):
+                d = [s[a] * ext[a] - anchor[a] for a in range(3)]
+                offs.add((round(float(np.dot(d, m)), 9), round(float(np.dot(d, n)), 9)))
+            a0 = x * float(m[0]) + y * float(m[1]) + z * float(m[2])
+            b0 = x * float(n[0]) + y * float(n[1]) + z * float(n[2])
+            rho = torch.full_like(best, float("inf"))
+            for oa, ob in sorted(offs):
+                rho = torch.minimum(rho, ((a0 + oa) / aspect).square() + (b0 + ob).square())
+            upd = rho < best
+            best = torch.where(upd, rho, best)
+            fam_of[upd] = fam + 1
+    target = int(round(v * best.numel()))
+    sigma = torch.sort(best.view(-1)).values[target - 1]
+    phase = torch.where(best <= sigma, fam_of, torch.zeros_like(fam_of)).contiguous()
+    k = [[km, km, km, 0.0, 0.0, 0.0]]
+    for u in axes:
+        t = kt * np.eye(3) + (ka - kt) * np.outer(u, u)
+        k.append([t[0, 0], t[1, 1], t[2, 2], t[0, 1], t[0, 2], t[1, 2]])
+    return phase, np.array(k)
+
+
+def _exchange_xz(phase, k):
+    """The cell with x and z exchanged: its x solve is the z solve of the cell."""
+    return phase.permute(2, 1, 0).contiguous(), k[:, [2, 1, 0, 5, 4, 3]].copy()
+
+
+def _rng(seed):
+    return np.random.default_rng([1503, seed])
+
+
+def _cell(case, rng):
+    return _braid(case["nx"], case["ny"], case["nz"], float(rng.uniform(20.0, 45.0)), float(rng.uniform(0.35, 0.6)))
+
+
+def _start_field(shape, axis, start, rng):
+    """None (zero start), the linear wall-to-wall profile, or that profile with
+    smooth deviations of a few per cent, as a learned start has them."""
+    if start == "zero":
+        return None
+    n = shape[2 - axis]
+    view = [1, 1, 1]
+    view[2 - axis] = n
+    s = ((torch.arange(n, device=DEV, dtype=torch.float64) + 0.5) / n).view(view)
+    T = (1.0 - s).expand(shape).clone()
+    if start == "smooth":
+        dev = torch.sin(math.pi * s) * float(rng.uniform(0.02, 0.06))
+        for a in range(3):
+            if a == axis:
+                continue
+            va = [1, 1, 1]
+            va[2 - a] = shape[2 - a]
+            t = ((torch.arange(shape[2 - a], device=DEV, dtype=torch.float64) + 0.5) / shape[2 - a]).view(va)
+            dev = dev * torch.cos(2.0 * math.pi * (int(rng.integers(1, 4)) * t + float(rng.uniform())))
+        T = T + dev
+    return T
+
+
+def _unit_cell_specs(count, nxy, rng):
+    """Braiding angle and fibre fraction of the unit-cell study (Eqs. 32-37)."""
+    out = []
+    for i in range(count):
+        gamma = (20.0, 25.0, 30.0, 35.0, 40.0, 45.0)[i % 6]
+        phi = (0.4, 0.5, 0.58)[i % 3] / 0.68
+        nz = int(round(nxy / math.tan(math.radians(gamma))))
+        gamma += float(rng.uniform(-1.0, 1.0))
+        lam_l = 7.81 * phi + 0.178 * (1.0 - phi)
+        lam_t = 0.178 + phi / (1.0 / (0.675 - 0.178) + (1.0 - phi) / (2.0 * 0.178))
+        out.append((nxy, nxy, nz + nz % 2, gamma, math.pi * math.sqrt(3.0) / 8.0, lam_l, lam_t, 0.178))
+    return out
+
+
+def _batch_media(case, rng):
+    """(phase, k, gradient axis) of every solve of a batch."""
+    if case["nxy"]:
+        return [_braid(*spec) + (0,) for spec in _unit_cell_specs(case["cells"], case["nxy"], rng)]
+    sizes = [int(v) for v in case["sizes"].split(",")]
+    # extents follow a fixed cycle, so that every seed has the same work
+    out = []
+    for i in range(case["cells"]):
+        n = [sizes[(i + j * (i // len(sizes) + 1)) % len(sizes)] for j in range(3)]
+        p, k = _braid(*n, float(rng.uniform(20.0, 45.0)), float(rng.uniform(0.35, 0.6)))
+        out.append((p, k, 0))
+        out.append(_exchange_xz(p, k) + (0,))
+    return out
+
+
+def _batch_shapes(case):
+    if case["nxy"]:
+        return [(s[2], s[1], s[0]) for s in _unit_cell_specs(case["cells"], case["nxy"], _rng(0))]
+    sizes = [int(v) for v in case["sizes"].split(",")]
+    out = []
+    for i in range(case["cells"]):
+        n = [sizes[(i + j * (i // len(sizes) + 1)) % len(sizes)] for j in range(3)]
+        out += [(n[2], n[1], n[0]), (n[0], n[1], n[2])]
+    return out
+
+
+def _training_state(net, rng):
+    """A network in the middle of its training: seeded weights, Adam's
+    moments as they are once the first gradients have averaged out."""
+    sd = net.state_dict()
+    sd["t"] = 200
+    for name, cin, cout, _ in ws.LAYERS:
+        w = sd["w"][name]
+        r = torch.from_numpy(rng.standard_normal(tuple(w.shape)).astype(np.float32))
+        r[:, 27 * cin:] = 0.0
+        sd["adam"]["mw"][name] = 1e-4 * r
+        sd["adam"]["vw"][name] = torch.full_like(w, 1e-6)
+        sd["adam"]["mb"][name] = torch.zeros(cout)
+        sd["adam"]["vb"][name] = torch.full((cout,), 1e-6)
+    return sd
+
+
+def _training_samples(case, rng):
+    phases, feats, targets = [], [], []
+    for _ in range(case["batch"]):
+        p, k = _cell(case, rng)
+        kmax = max(np.linalg.eigvalsh([[r[0], r[3], r[4]], [r[3], r[1], r[5]], [r[4], r[5], r[2]]])[-1] for r in k)
+        phases.append(p.view(-1))
+        feats.append(torch.from_numpy((k / kmax).astype(np.float32)).to(DEV))
+        T = _start_field(p.shape, 0, "smooth", rng) - _start_field(p.shape, 0, "linear", rng)
+        targets.append((ws.SCALE * T).to(torch.float32).view(-1))
+    return phases, feats, targets
+
+
+# ---------------------------------------------------------------------------
+# prepare, run
+# ---------------------------------------------------------------------------
+
+
+def _medium(phase, k, prec, storage, axis, sides):
+    g = solver.Medium(phase, k, precision=prec, device=DEV, storage=storage)
+    g.load_tuned(TUNED)
+    g.set_bc(axis, 1.0, 0.0, (sides,) * 3)
+    return g
+
+
+def prepare(case, seed):
+    rng = _rng(seed)
+    kind = case["kind"]
+    if kind == "solve":
+        phase, k = _cell(case, rng)
+        g = _medium(phase, k, case["prec"], case["storage"], case["axis"], case["sides"])
+        T0 = _start_field(g.shape, case["axis"], case["start"], rng)
+        return dict(kind=kind, g=g, T0=None if T0 is None else T0.to(g.dtype), steps=case["steps"])
+    if kind == "batch":
+        cells, starts = [], []
+        for phase, k, axis in _batch_media(case, rng):
+            g = solver.Medium(phase, k, precision="f32", device=DEV, storage="moments")
+            g.set_bc(axis, 1.0, 0.0, ("periodic",) * 3)
+            cells.append(g)
+            T0 = _start_field(g.shape, axis, case["start"], rng)
+            starts.append(None if T0 is None else T0.to(g.dtype))
+        if case["tune"]:
+            solver.batch_autotune(cells)
+        return dict(kind=kind, cells=cells, starts=starts, steps=case["steps"])
+    if kind == "observe":
+        phase, k = _cell(case, rng)
+        g = _medium(phase, k, case["prec"], case["storage"], 0, "periodic")
+        g.init(_start_field(g.shape, 0, "smooth", rng).to(g.dtype), flux=True)
+        g.step(100)
+        return dict(kind=kind, g=g)
+    if kind == "predict":
+        phase, k = _cell(case, rng)
+        g = _medium(phase, k, "f32", "moments", 0, "periodic")
+        return dict(kind=kind, g=g, m=types.SimpleNamespace(phase=phase, k=k), net=ws.Net.from_file(MODEL, batch=1))
+    net = ws.Net(n=64, batch=case["batch"], seed=seed % 1000)
+    net.load_state_dict(_training_state(net, rng))
+    phases, feats, targets = _training_samples(case, rng)
+    return dict(kind=kind, net=net, shape=(case["nz"], case["ny"], case["nx"]), phases=phases, feats=feats,
+                targets=targets)
+
+
+def run(state):
+    kind = state["kind"]
+    if kind == "solve":
+        g = state["g"]
+        if state["T0"] is None:
+            g.init()
+        else:
+            g.init(state["T0"], flux=True)
+        r = g.solve(1e-12, "keff", state["steps"], check_every=200)
+        return {"T": g.temperature(), **{k: r[k] for k in OBSERVED}}
+    if kind == "batch":
+        for g, T0 in zip(state["cells"], state["starts"]):
+            if T0 is None:
+                g.init()
+            else:
+                g.init(T0, flux=True)
+        res, _ = solver.batch_solve(state["cells"], 1e-12, "keff", state["steps"], check_every=200)
+        return {"T": torch.cat([g.temperature().view(-1) for g in state["cells"]]),
+                "observed": np.array([[r[k] for k in OBSERVED] for r in res])}
+    if kind == "observe":
+        g = state["g"]
+        r = g.keff()
+        return {"T": g.temperature(), "q": g.flux(), **{k: r[k] for k in OBSERVED}}
+    if kind == "predict":
+        T0, bad = ws.predict_start(state["net"], state["m"], state["g"])
+        return {"T0": T0, "rejected": bad}
+    net = state["net"]
+    nv = state["phases"][0].numel()
+    for b in range(net.batch):
+        net.set_input(b, state["phases"][b], state["feats"][b], state["shape"])
+        net.target[b * nv:(b + 1) * nv].copy_(state["targets"][b])
+    net.forward()
+    net.loss_and_grad()
+    net.backward()
+    net.adam(lr=5e-4)
+    return {"loss": net.loss, "gw": list(net.gw.values()), "gb": list(net.gb.values()), "w": list(net.w32.values()),
+            "b": list(net.b32.values())}
+
+
+# ---------------------------------------------------------------------------
+# work: what the path cannot do without
+# ---------------------------------------------------------------------------
+
+
+def _solve_work(nodes, steps, real):
+    """A solve reads its start field and phases once and writes the temperature
+    once; how often the state between them goes through memory is the
+    implementation's choice.  About 60 additions, products and conversions per
+    node and step."""
+    return {"bytes": nodes * (2 * real + 1), "flops": 60 * nodes * steps}
+
+
+def _net_work(grid, batch, train):
+    """Products of the convolutions; weights and the input and output of the
+    whole pass moved once, and each layer's activations once out and once in."""
+    d, h, w = grid
+    vox = [batch * (d >> lv) * (h >> lv) * (w >> lv) for lv in range(4)]
+    flops = bytes_ = 0
+    for name, cin, cout, _ in ws.LAYERS:
+        v = vox[ws.LEVEL[name]]
+        f = 2 * v * 27 * cin * cout
+        flops += f * ((2 if name == "c00" else 3) if train else 1)
+        bytes_ += 2 * (v * (cin + cout) + 27 * cin * cout) * (3 if train else 1)
+        if train:
+            bytes_ += 4 * 7 * 27 * cin * cout  # gradient, weights and Adam's moments
+    return flops, bytes_
+
+
+def work(case):
+    kind = case["kind"]
+    if kind == "batch":
+        return _solve_work(sum(a * b * c for a, b, c in _batch_shapes(case)), case["steps"], 4)
+    nodes = case["nx"] * case["ny"] * case["nz"]
+    if kind == "solve":
+        return _solve_work(nodes, case["steps"], 8 if case["prec"] == "f64" else 4)
+    if kind == "observe":
+        real = 8 if case["prec"] == "f64" else 4
+        v = 4 if case["storage"] == "moments" else 7
+        return {"bytes": nodes * ((v + 4) * real + 1), "flops": 120 * nodes}
+    if kind == "predict":
+        f, b = _net_work(ws.inference_grid((case["nz"], case["ny"], case["nx"]), 64), 1, False)
+        return {"bytes": b + 5 * nodes, "flops": f}
+    f, b = _net_work((case["nz"], case["ny"], case["nx"]), case["batch"], True)
+    return {"bytes": b, "flops": f}
+
+
+# ---------------------------------------------------------------------------
+# exact: the same in 64 bits, by plain torch
+# ---------------------------------------------------------------------------
+
+
+class _Lattice:
+    """The D3Q7 scheme with tau_0 = tau_4..6 = 1 in FP64, state (T, jhat)."""
+
+    def __init__(self, phase, k, axis, sides):
+        self.shape, self.axis = tuple(phase.shape), axis
+        self.per = [a != axis and sides == "periodic" for a in range(3)]
+        full = [np.array([[r[0], r[3], r[4]], [r[3], r[1], r[5]], [r[4], r[5], r[2]]]) for r in k]
+        self.s = 0.25 / max(np.linalg.eigvalsh(f)[-1] for f in full)
+        tau = [0.5 * np.eye(3) + self.s * f / 0.25 for f in full]
+        a = np.stack([np.eye(3) - np.linalg.inv(t) for t in tau])
+        m = np.stack([t - np.eye(3) for t in tau])
+        ids = phase.long()
+        pick = lambda t, i, j: torch.from_numpy(t[:, i, j].copy()).to(DEV)[ids]  # noqa: E731
+        pairs = ((0, 0), (1, 1), (2, 2), (0, 1), (0, 2), (1, 2))
+        self.a = {p: pick(a, *p) for p in pairs}
+        self.m = {p: pick(m, *p) for p in pairs}
+
+    def _apply(self, t, v):
+        at = lambda i, j: t[(min(i, j), max(i, j))]  # noqa: E731
+        return [at(i, 0) * v[0] + at(i, 1) * v[1] + at(i, 2) * v[2] for i in range(3)]
+
+    def _ends(self, a):
+        d, n = 2 - a, self.shape[2 - a]
+        return d, n
+
+    def init(self, T0):
+        if T0 is None:
+            self.T = torch.zeros(self.shape, dtype=torch.float64, device=DEV)
+            self.j = [torch.zeros_like(self.T) for _ in range(3)]
+            return
+        self.T = T0.double()
+        grad = []
+        for a in range(3):
+            d, n = self._ends(a)
+            lo, hi = torch.roll(self.T, 1, d), torch.roll(self.T, -1, d)
+            dist = torch.full([n if i == d else 1 for i in range(3)], 2.0, dtype=torch.float64, device=DEV)
+            if not self.per[a]:
+                first, last = self.T.narrow(d, 0, 1), self.T.narrow(d, n - 1, 1)
+                grad_axis = a == self.axis
+                lo.narrow(d, 0, 1).copy_(torch.ones_like(first) if grad_axis else first)
+                hi.narrow(d, n - 1, 1).copy_(torch.zeros_like(last) if grad_axis else last)
+                if grad_axis:
+                    dist.narrow(d, 0, 1).sub_(0.5)
+                    dist.narrow(d, n - 1, 1).sub_(0.5)
+            grad.append((hi - lo) / dist)
+        self.j = [-0.25 * v for v in self._apply(self.m, grad)]
+
+    def pull(self):
+        """Populations arriving at every node and the ones leaving at the walls."""
+        e = self.T / 8
+        arr, wall = [], None
+        for a in range(3):
+            d, n = self._ends(a)
+            plus, minus = e + self.j[a] / 2, e - self.j[a] / 2
+            lo, hi = torch.roll(plus, 1, d), torch.roll(minus, -1, d)
+            if not self.per[a]:
+                out_lo, out_hi = minus.narrow(d, 0, 1), plus.narrow(d, n - 1, 1)
+                if a == self.axis:
+                    wall = (out_lo, out_hi)
+                    lo.narrow(d, 0, 1).copy_(0.25 - out_lo)
+                    hi.narrow(d, n - 1, 1).copy_(-out_hi)
+                else:
+                    lo.narrow(d, 0, 1).copy_(out_lo)
+                    hi.narrow(d, n - 1, 1).copy_(out_hi)
+            arr += [lo, hi]
+        T = self.T / 4 + arr[0] + arr[1] + arr[2] + arr[3] + arr[4] + arr[5]
+        j = [arr[0] - arr[1], arr[2] - arr[3], arr[4] - arr[5]]
+        return T, j, self._apply(self.a, j), wall
+
+    def step(self, n):
+        for _ in range(n):
+            self.T, _, self.j, _ = self.pull()
+
+    def observe(self):
+        T, j, jh, (hot, cold) = self.pull()
+        ng, dT = self.shape[2 - self.axis], 1.0
+        area = self.T.numel() / ng
+        c = ng / (dT * area * self.s)
+        k_hot = float((0.25 - 2 * hot).sum()) * c
+        k_cold = float((2 * cold).sum()) * c
+        q = [0.5 * (j[a] + jh[a]) for a in range(3)]
+        return T, jh, q, {"keff": 0.5 * (k_hot + k_cold), "keff_hot": k_hot, "keff_cold": k_cold,
+                          "keff_vol": float(q[self.axis].mean()) * ng / (dT * self.s), "temp_mean": float(T.mean())}
+
+    def solve(self, T0, steps):
+        self.init(T0)
+        self.step(steps - 1)
+        self.T, self.j, _, obs = self.observe()
+        return obs
+
+
+def _conv(x, w, b, relu):
+    """3x3x3 convolution of x [n][D][H][W][c], zero outside x, periodic in y and z."""
+    n, D, H, W, cin = x.shape
+    xp = torch.nn.functional.pad(x, (0, 0, 1, 1))
+    xp = torch.cat([xp[:, :, -1:], xp, xp[:, :, :1]], 2)
+    xp = torch.cat([xp[:, -1:], xp, xp[:, :1]], 1)
+    acc = b
+    for tap in range(27):
+        dz, dy, dx = tap // 9, tap // 3 % 3, tap % 3
+        v = xp[:, dz:dz + D, dy:dy + H, dx:dx + W].reshape(-1, cin)
+        acc = acc + v @ w[:, tap * cin:(tap + 1) * cin].t()
+    acc = acc.view(n, D, H, W, -1)
+    return torch.relu(acc) if relu else acc
+
+
+def _network(x, w, b):
+    def conv(name, v):
+        return _conv(v, w[name], b[name], name != "c04")
+
+    def pool(v):
+        n, D, H, W, c = v.shape
+        return v.view(n, D // 2, 2, H // 2, 2, W // 2, 2, c).mean((2, 4, 6))
+
+    def up(v):
+        return v.repeat_interleave(2, 1).repeat_interleave(2, 2).repeat_interleave(2, 3)
+
+    e0 = conv("c01", conv("c00", x))
+    e1 = conv("c11", conv("c10", pool(e0)))
+    e2 = conv("c21", conv("c20", pool(e1)))
+    e3 = conv("c31", conv("c30", pool(e2)))
+    d2 = conv("c23", conv("c22", up(e3)) + e2)
+    d1 = conv("c13", conv("c12", up(d2)) + e1)
+    return conv("c04", conv("c03", conv("c02", up(d1)) + e0))
+
+
+def _features(phase, feat, grid):
+    """Box averages of the per-voxel features on the network's grid."""
+    v = torch.cat([feat[phase.long()], torch.zeros(tuple(phase.shape) + (2,), dtype=torch.float64, device=DEV)], -1)
+    for ax, nc in enumerate(grid):
+        n = v.shape[ax]
+        rows = torch.zeros((nc, n), dtype=torch.float64, device=DEV)
+        own = ((2 * torch.arange(n) + 1) * nc) // (2 * n)
+        rows[own.to(DEV), torch.arange(n, device=DEV)] = 1.0
+        for c in range(nc):
+            if not (own == c).any():
+                rows[c, ((2 * c + 1) * n) // (2 * nc)] = 1.0
+        rows /= rows.sum(1, keepdim=True)
+        v = torch.moveaxis(torch.tensordot(rows, torch.moveaxis(v, ax, 0), 1), 0, ax)
+    x = (torch.arange(grid[2], device=DEV, dtype=torch.float64) + 0.5) / grid[2] - 0.5
+    v = v.contiguous()
+    v[..., 6] = x
+    return v
+
+
+def _interpolate(p, shape):
+    """Trilinear between voxel centres: periodic in z and y, clamped in x."""
+    for ax in range(3):
+        nc, n = p.shape[ax], shape[ax]
+        c = (torch.arange(n, device=DEV, dtype=torch.float64) + 0.5) * nc / n - 0.5
+        f = torch.floor(c)
+        t = c - f
+        lo, hi = f.long(), f.long() + 1
+        if ax == 2:
+            lo, hi = lo.clamp(0, nc - 1), hi.clamp(0, nc - 1)
+        else:
+            lo, hi = lo % nc, hi % nc
+        view = [1, 1, 1]
+        view[ax] = n
+        p = p.index_select(ax, lo) * (1 - t).view(view) + p.index_select(ax, hi) * t.view(view)
+    return p
+
+
+def exact(case, seed):
+    rng = _rng(seed)
+    kind = case["kind"]
+    with torch.no_grad():
+        if kind == "solve":
+            phase, k = _cell(case, rng)
+            T0 = _start_field(tuple(phase.shape), case["axis"], case["start"], rng)
+            if T0 is not None and case["prec"] == "f32":
+                T0 = T0.float()
+            lat = _Lattice(phase, k, case["axis"], case["sides"])
+            obs = lat.solve(T0, case["steps"])
+            return {"T": lat.T, **obs}
+        if kind == "batch":
+            fields, rows = [], []
+            for phase, k, axis in _batch_media(case, rng):
+                T0 = _start_field(tuple(phase.shape), axis, case["start"], rng)
+                lat = _Lattice(phase, k, axis, "periodic")
+                obs = lat.solve(None if T0 is None else T0.float(), case["steps"])
+                fields.append(lat.T.reshape(-1))
+                rows.append([obs[o] for o in OBSERVED])
+            return {"T": torch.cat(fields), "observed": np.array(rows)}
+        if kind == "observe":
+            phase, k = _cell(case, rng)
+            T0 = _start_field(tuple(phase.shape), 0, "smooth", rng)
+            lat = _Lattice(phase, k, 0, "periodic")
+            lat.init(T0.float() if case["prec"] == "f32" else T0)
+            lat.step(100)
+            _, _, q, obs = lat.observe()
+            return {"T": lat.T, "q": torch.stack(q) / lat.s, **obs}
+        if kind == "predict":
+            phase, k = _cell(case, rng)
+            shape = tuple(phase.shape)
+            sd = torch.load(MODEL, map_location=DEV, weights_only=True)
+            grid = ws.inference_grid(shape, int(sd["n"]))
+            sp = [shape[2] / grid[2], shape[1] / grid[1], shape[0] / grid[0]]
+            kk = np.array([[r[i] / (sp[a] * sp[b]) for i, (a, b) in
+                            enumerate(((0, 0), (1, 1), (2, 2), (0, 1), (0, 2), (1, 2)))] for r in k])
+            kmax = max(np.linalg.eigvalsh([[r[0], r[3], r[4]], [r[3], r[1], r[5]], [r[4], r[5], r[2]]])[-1] for r in kk)
+            x = _features(phase, torch.from_numpy(kk / kmax).to(DEV), grid)
+            w = {n: t.to(torch.bfloat16).double() for n, t in sd["w"].items()}
+            b = {n: t.double() for n, t in sd["b"].items()}
+            p = _interpolate(_network(x.unsqueeze(0), w, b)[0, ..., 0], shape)
+            return {"T0": _start_field(shape, 0, "linear", rng) + p / ws.SCALE, "rejected": None}
+    # one training iteration by autograd
+    net = ws.Net(n=64, batch=1, seed=seed % 1000)
+    sd = _training_state(net, rng)
+    del net
+    phases, feats, targets = _training_samples(case, rng)
+    shape = (case["nz"], case["ny"], case["nx"])
+    w = {n: t.to(DEV).to(torch.bfloat16).double().requires_grad_(True) for n, t in sd["w"].items()}
+    b = {n: t.to(DEV).double().requires_grad_(True) for n, t in sd["b"].items()}
+    loss = 0.0
+    for p, f, t in zip(phases, feats, targets):
+        x = _features(p.view(shape), f.double(), shape)
+        out = _network(x.unsqueeze(0), w, b)[0, ..., 0].reshape(-1)
+        part = (out - t.double()).square().sum() / (t.numel() * case["batch"])
+        part.backward()
+        loss += float(part.detach())
+    t = sd["t"] + 1
+    new = {}
+    for key, grads, mom, var in (("w", w, "mw", "vw"), ("b", b, "mb", "vb")):
+        new[key] = []
+        for name, *_ in ws.LAYERS:
+            g = grads[name].grad
+            m = 0.9 * sd["adam"][mom][name].to(DEV).double() + 0.1 * g
+            v = 0.999 * sd["adam"][var][name].to(DEV).double() + 0.001 * g * g
+            new[key].append(sd[key][name].to(DEV).double()
+                            - 5e-4 * (m / (1 - 0.9 ** t)) / (torch.sqrt(v / (1 - 0.999 ** t)) + 1e-8))
+    return {"loss": torch.tensor([loss]), "gw": [w[n].grad for n, *_ in ws.LAYERS],
+            "gb": [b[n].grad for n, *_ in ws.LAYERS], "w": new["w"], "b": new["b"]}
