@@ -85,7 +85,7 @@ def draw(rng):
         prec = rng.choice(["f32", "f32", "f64"])
         storage = rng.choice(["moments", "moments", "populations"])
         return _solve("", n, prec, storage, rng.choice([0, 1, 2]), rng.choice(["periodic", "adiabatic"]),
-                      rng.choice(["smooth", "zero"]))
+                      rng.choice(["smooth", "linear"]))
     if kind == "batch":
         if rng.random() < 0.25:
             return dict(kind="batch", cells=rng.randint(2, 9), nxy=rng.choice([32, 40, 48, 56, 64]), sizes="",
