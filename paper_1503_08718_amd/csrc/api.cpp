@@ -17,6 +17,7 @@
 
 #include "lbm_internal.h"
 #include "medium.h"
+#include "step2_internal.h"
 
 using namespace mrt;
 
@@ -329,6 +330,7 @@ extern "C" mrtlbm_status mrtlbm_create(int nx, int ny, int nz, const unsigned ch
     m->pcap = partial_capacity(nx, ny);
     m->stream = (hipStream_t)hip_stream;
     m->launch = default_launch(m);
+    m->pair = p == MRTLBM_F64 ? step2_shape<double>(nx, ny, nz, nphase) : step2_shape<float>(nx, ny, nz, nphase);
     hipError_t e = hipGetDevice(&m->device);
     if (e == hipSuccess) e = hipHostMalloc((void **)&m->pinned, 256, hipHostMallocDefault);
     if (e != hipSuccess) {
@@ -442,6 +444,7 @@ extern "C" mrtlbm_status mrtlbm_set_launch(mrtlbm_medium *m, const mrtlbm_launch
         return fail(MRTLBM_E_ARG, "launch shape vec=%d bx=%d by=%d nt=%d not admissible", L.vec, L.bx, L.by, L.nt);
     drop_graphs(m);
     m->launch = L;
+    m->single = launch != nullptr;
     return MRTLBM_OK;
 }
 
@@ -449,8 +452,21 @@ extern "C" mrtlbm_status mrtlbm_set_launch(mrtlbm_medium *m, const mrtlbm_launch
 // stepping
 // ---------------------------------------------------------------------------
 
+// n steps, in pairs where the medium takes two steps per pass; even: an even
+// number of pairs, so that the buffers have changed places as often as n
+// single steps would have them (a captured graph is replayed from one buffer)
 template <typename real>
-static hipError_t plain_steps(mrtlbm_medium *m, long long n, hipStream_t s, int *cur) {
+hipError_t mrt::plain_steps(mrtlbm_medium *m, long long n, bool even, hipStream_t s, int *cur) {
+    const Step2Shape &g = m->pair;
+    if (g.vec && !m->single && step2_takes<real>(make_cell<real>(m, *cur))) {
+        const long long pairs = even ? n / 4 * 2 : n / 2;
+        for (long long i = 0; i < pairs; i++) {
+            hipError_t e = launch_step2<real>(make_cell<real>(m, *cur), g, s);
+            if (e != hipSuccess) return e;
+            *cur ^= 1;
+        }
+        n -= 2 * pairs;
+    }
     for (long long i = 0; i < n; i++) {
         hipError_t e = launch_step<real>(make_cell<real>(m, *cur), m->launch, s);
         if (e != hipSuccess) return e;
@@ -458,6 +474,8 @@ static hipError_t plain_steps(mrtlbm_medium *m, long long n, hipStream_t s, int 
     }
     return hipSuccess;
 }
+template hipError_t mrt::plain_steps<float>(mrtlbm_medium *, long long, bool, hipStream_t, int *);
+template hipError_t mrt::plain_steps<double>(mrtlbm_medium *, long long, bool, hipStream_t, int *);
 
 template <typename real>
 static hipError_t check_step(mrtlbm_medium *m, int mode, hipStream_t s, int *cur, void *qout, double qscale) {
@@ -485,7 +503,7 @@ static mrtlbm_status get_graph(mrtlbm_medium *m, int K, bool with_check, hipGrap
     if (!m->cap_stream) HIPCHK(hipStreamCreateWithFlags(&m->cap_stream, hipStreamNonBlocking));
     HIPCHK(hipStreamBeginCapture(m->cap_stream, hipStreamCaptureModeThreadLocal));
     int cur = m->cur;
-    hipError_t e = plain_steps<real>(m, with_check ? K - 1 : K, m->cap_stream, &cur);
+    hipError_t e = plain_steps<real>(m, with_check ? K - 1 : K, true, m->cap_stream, &cur);
     if (e == hipSuccess && with_check) e = check_step<real>(m, 1, m->cap_stream, &cur, nullptr, 0.0);
     if (e == hipSuccess && with_check)
         e = hipMemcpyAsync(m->pinned, m->final8, NRED * sizeof(double), hipMemcpyDeviceToHost, m->cap_stream);
@@ -519,7 +537,7 @@ static mrtlbm_status do_steps(mrtlbm_medium *m, long long nsteps) {
         for (; done + G <= nsteps; done += G) HIPCHK(hipGraphLaunch(ge, m->stream));
     }
     int cur = m->cur;
-    HIPCHK(plain_steps<real>(m, nsteps - done, m->stream, &cur));
+    HIPCHK(plain_steps<real>(m, nsteps - done, false, m->stream, &cur));
     m->cur = cur;
     m->steps += nsteps;
     return MRTLBM_OK;
@@ -681,7 +699,7 @@ static mrtlbm_status do_solve(mrtlbm_medium *m, double tol, mrtlbm_tol_kind kind
             m->steps += K;
         } else {
             int cur = m->cur;
-            HIPCHK(plain_steps<real>(m, left - 1, m->stream, &cur));
+            HIPCHK(plain_steps<real>(m, left - 1, false, m->stream, &cur));
             HIPCHK(check_step<real>(m, 1, m->stream, &cur, nullptr, 0.0));
             HIPCHK(hipMemcpyAsync(m->pinned, m->final8, NRED * sizeof(double), hipMemcpyDeviceToHost, m->stream));
             m->cur = cur;
@@ -803,6 +821,7 @@ extern "C" mrtlbm_status mrtlbm_autotune(mrtlbm_medium *m, const char *cache_pat
     Launch bestL = m->launch;
     double bestms = 1e300;
     const Launch saved = m->launch;
+    m->single = true;  // the shape is the single step's
     for (int vec : {4, 2, 1})
         for (int bx : {8, 16, 32, 64})
             for (int t : {64, 128, 256})
@@ -819,6 +838,7 @@ extern "C" mrtlbm_status mrtlbm_autotune(mrtlbm_medium *m, const char *cache_pat
                 if (st == MRTLBM_OK) st = mrtlbm_time_steps(m, n, &ms);
                 if (st != MRTLBM_OK) {
                     m->launch = saved;
+                    m->single = false;
                     return st;
                 }
                 if (ms < bestms) {
@@ -827,6 +847,7 @@ extern "C" mrtlbm_status mrtlbm_autotune(mrtlbm_medium *m, const char *cache_pat
                 }
             }
     m->launch = bestL;
+    m->single = false;
     drop_graphs(m);
     m->initialised = false;
     if (best) {
@@ -864,6 +885,7 @@ extern "C" mrtlbm_status mrtlbm_load_tuned(mrtlbm_medium *m, const char *cache_p
         if (r >> L.vec >> L.bx >> L.by >> L.nt >> L.map && launch_ok(m, L)) {
             drop_graphs(m);
             m->launch = L;
+            m->single = false;
             return MRTLBM_OK;
         }
     }

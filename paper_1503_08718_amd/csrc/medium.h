@@ -7,6 +7,7 @@
 
 #include "../../include/mrtlbm.h"
 #include "lbm_internal.h"
+#include "step2_internal.h"
 
 namespace mrt {
 
@@ -69,6 +70,8 @@ struct mrtlbm_medium {
     long long steps = 0;
     bool initialised = false;
     mrt::Launch launch{4, 64, 4, 0, 0};
+    mrt::Step2Shape pair;      // how two steps per pass are cut into blocks
+    bool single = false;       // every step its own launch, in the shape the caller set
     std::vector<mrt::GraphEntry> graphs;
 };
 
@@ -78,6 +81,8 @@ Launch default_launch(const mrtlbm_medium *m);
 template <typename real>
 Cell<real> make_cell(const mrtlbm_medium *m, int cur);
 void drop_graphs(mrtlbm_medium *m);
+template <typename real>
+hipError_t plain_steps(mrtlbm_medium *m, long long n, bool even, hipStream_t s, int *cur);
 void fill_result(const mrtlbm_medium *m, const double *f, mrtlbm_result *out);
 int stop_rule(StopState &ss, const mrtlbm_result &r, double tol, mrtlbm_tol_kind kind);
 bool has_side_flux(const mrtlbm_medium *m);

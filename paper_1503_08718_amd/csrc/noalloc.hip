@@ -74,13 +74,10 @@ static mrtlbm_status solve_noalloc(mrtlbm_medium *m, double tol, mrtlbm_tol_kind
         const long long left = max_steps - m->steps;
         const long long block = left >= K ? K : left;
         int cur = m->cur;
-        for (long long i = 0; i + 1 < block; i++) {
-            hipError_t e = launch_step<real>(make_cell<real>(m, cur), m->launch, m->stream);
-            if (e != hipSuccess) return hip_fail(e, "step kernel");
-            cur ^= 1;
-        }
+        hipError_t e = plain_steps<real>(m, block - 1, false, m->stream, &cur);
+        if (e != hipSuccess) return hip_fail(e, "step kernel");
         int nb = 0;
-        hipError_t e = launch_check<real>(make_cell<real>(m, cur), m->launch, 1, partials, &nb, nullptr, 0.0, m->stream);
+        e = launch_check<real>(make_cell<real>(m, cur), m->launch, 1, partials, &nb, nullptr, 0.0, m->stream);
         if (e == hipSuccess) e = launch_reduce(partials, nb, final8, m->stream);
         if (e == hipSuccess)
             e = hipMemcpyAsync(m->pinned, final8, NRED * sizeof(double), hipMemcpyDeviceToHost, m->stream);

@@ -1,0 +1,151 @@
+// The two-steps-per-pass kernel (step2_device.hpp) for one cell, and how a
+// cell is cut into blocks for it.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "step2_device.hpp"
+#include "step2_internal.h"
+
+namespace mrt {
+
+constexpr int STEP2_LDS = 160 * 1024;
+constexpr int STEP2_CUS = 256;
+// state beyond the 256 MB last-level cache is written past it
+constexpr size_t STEP2_CACHE = 256u << 20;
+
+// threads of the largest block: what the registers of a vector allow
+template <typename real, int VEC>
+constexpr int step2_max_threads() {
+    return sizeof(real) * VEC > 16 ? 512 : 1024;
+}
+
+template <typename real, int VEC, bool RAG, int NT, int GA>
+__global__ void __launch_bounds__((step2_max_threads<real, VEC>())) k_step2(Cell<real> c, int tr, int ntiles, int nchunks) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    // blocks go to the 8 XCDs round robin: each XCD takes a run of
+    // neighbouring tiles, whose halo rows meet in its L2
+    const int nb = ntiles * nchunks, per = (nb + 7) / 8;
+    const int b = (int)(blockIdx.x % 8u) * per + (int)(blockIdx.x / 8u);
+    if (b >= nb || (int)(blockIdx.x / 8u) >= per) return;
+    const int tile = b % ntiles, chunk = b / ntiles;
+    const int y0 = tile * tr;
+    const int z0 = (int)((long long)chunk * c.nz / nchunks), z1 = (int)((long long)(chunk + 1) * c.nz / nchunks);
+    march2<real, VEC, RAG, NT, GA>(c, reinterpret_cast<real *>(smem_raw), tr, y0, min(tr, c.ny - y0), z0, z1 - z0);
+}
+
+// Time of one launch in microseconds, as measured at 64^3 to 256^3 and with
+// launches that leave the card idle (128^3 in FP32: 46.5, 36.8, 22.5 and 21.0
+// with 60, 80, 255 and 256 blocks).  A block starts and drains in 7; an
+// iteration takes 0.45 and the arithmetic of the waves that share a SIMD (one
+// vector through both steps: 0.84 for 4 FP32 nodes, 0.48 and 0.84 for 2 and 4
+// FP64 nodes); the first and last plane cost half an iteration each; more
+// blocks than the card holds take another round.
+static double step2_model(double per_wave, int rows, int rpw, long long blocks, int occ, int planes) {
+    const int k = (int)std::min<long long>(occ, (blocks + STEP2_CUS - 1) / STEP2_CUS);
+    const long long rounds = (blocks + (long long)STEP2_CUS * occ - 1) / ((long long)STEP2_CUS * occ);
+    // rows + 2 rows take the first step, rows the second
+    const double busy = (rows + 1.0) / rpw * k / 4.0;
+    return rounds * (7.0 + (planes + 1) * (per_wave * busy + 0.45));
+}
+
+// nodes per thread: a row of nx nodes has to fit one wave
+static int step2_vec(int real_bytes, int nx) { return real_bytes == 4 ? 4 : (nx <= 128 ? 2 : 4); }
+
+template <typename real>
+bool step2_takes(const Cell<real> &c) {
+    if (!c.storage || c.relax) return false;
+    // imposed side fluxes would add to every pulled wall population
+    for (int a = 0; a < 3; a++)
+        if (c.phi[a][0] != 0 || c.phi[a][1] != 0) return false;
+    return true;
+}
+
+template <typename real>
+Step2Shape step2_shape(int nx, int ny, int nz, int nphase) {
+    Step2Shape best;
+    const long long N = (long long)nx * ny * nz;
+    // a row in one wave, 32-bit node numbers and byte offsets in a plane, and
+    // no extent of 1 (the halo rows and planes wrap around once)
+    const int vec = step2_vec(sizeof(real), nx);
+    if (nx < vec || nx > 64 * vec || ny < 2 || nz < 2 || N >= (1LL << 31) || (long long)nx * ny >= (1LL << 28)) return best;
+    const int nxv = (nx + vec - 1) / vec, rpw = 64 / nxv, len = nxv * vec;
+    const int maxw = (sizeof(real) * vec > 16 ? 512 : 1024) / 64;
+    const double per_wave = sizeof(real) == 8 && vec == 2 ? 0.48 : 0.84;
+    // two single steps: 2.4 us each and 5.5 (FP32) or 9 (FP64) us per million
+    // nodes with vectors of 4 and 2 nodes, three times that with single nodes
+    const int single_vec = nx % 4 == 0 ? 4 : (nx % 2 == 0 ? 2 : 1);
+    const double slope = (sizeof(real) == 4 ? 5.5 : 9.0) * (single_vec == 1 ? 3.0 : 1.0);
+    double tmin = 2.0 * (2.4 + slope * 1e-6 * (double)N);
+    for (int w = 1; w <= maxw; w++) {
+        int tr = std::min(w * rpw - 4, ny);
+        if (tr < 1) continue;
+        const int ntiles = (ny + tr - 1) / tr;
+        tr = (ny + ntiles - 1) / ntiles;
+        const size_t lds = sizeof(real) * (size_t)step2_lds_reals(tr, len, nphase);
+        if (lds > (size_t)STEP2_LDS) continue;
+        const int waves = (tr + 4 + rpw - 1) / rpw;
+        const int occ = std::min(maxw / waves, (int)(STEP2_LDS / lds));
+        int before = 0;
+        for (int planes = nz; planes >= 1; planes--) {
+            const int nchunks = (nz + planes - 1) / planes;
+            if (nchunks == before) continue;  // the fewest planes of each count
+            before = nchunks;
+            const int per = (nz + nchunks - 1) / nchunks;
+            const double t = step2_model(per_wave, tr, rpw, (long long)ntiles * nchunks, occ, per);
+            if (t < tmin) {
+                tmin = t;
+                best.vec = vec;
+                best.tr = tr;
+                best.ntiles = ntiles;
+                best.nchunks = nchunks;
+                best.threads = waves * 64;
+                best.lds = lds;
+            }
+        }
+    }
+    return best;
+}
+
+template <typename real, int VEC, bool RAG, int GA>
+static void launch_step2_a(const Cell<real> &c, const Step2Shape &g, hipStream_t s) {
+    const dim3 grid((unsigned)((g.ntiles * g.nchunks + 7) / 8 * 8)), block(g.threads);
+    // 256^3 FP32 (537 MB): 55.2 us per step with non-temporal stores, 58.6
+    // without; 192^3 (226 MB): 27.9 and 25.7; 128^3 FP64 (134 MB): 16.1 and 13.4
+    if (8 * sizeof(real) * (size_t)c.N > STEP2_CACHE)
+        hipLaunchKernelGGL((k_step2<real, VEC, RAG, 2, GA>), grid, block, g.lds, s, c, g.tr, g.ntiles, g.nchunks);
+    else
+        hipLaunchKernelGGL((k_step2<real, VEC, RAG, 0, GA>), grid, block, g.lds, s, c, g.tr, g.ntiles, g.nchunks);
+}
+
+template <typename real, int VEC, bool RAG>
+static void launch_step2_v(const Cell<real> &c, const Step2Shape &g, hipStream_t s) {
+    if (c.gaxis == 0) launch_step2_a<real, VEC, RAG, 0>(c, g, s);
+    else if (c.gaxis == 1) launch_step2_a<real, VEC, RAG, 1>(c, g, s);
+    else launch_step2_a<real, VEC, RAG, 2>(c, g, s);
+}
+
+template <typename real>
+hipError_t launch_step2(const Cell<real> &c, const Step2Shape &g, hipStream_t s) {
+    const bool rag = c.nx % g.vec != 0;
+    if constexpr (sizeof(real) == 4) {
+        if (rag) launch_step2_v<real, 4, true>(c, g, s);
+        else launch_step2_v<real, 4, false>(c, g, s);
+    } else if (g.vec == 2) {
+        if (rag) launch_step2_v<real, 2, true>(c, g, s);
+        else launch_step2_v<real, 2, false>(c, g, s);
+    } else {
+        if (rag) launch_step2_v<real, 4, true>(c, g, s);
+        else launch_step2_v<real, 4, false>(c, g, s);
+    }
+    return hipGetLastError();
+}
+
+#define MRT_INST2(real)                                                                                            \
+    template bool step2_takes<real>(const Cell<real> &);                                                           \
+    template Step2Shape step2_shape<real>(int, int, int, int);                                                     \
+    template hipError_t launch_step2<real>(const Cell<real> &, const Step2Shape &, hipStream_t);
+MRT_INST2(float)
+MRT_INST2(double)
+
+}  // namespace mrt
