@@ -50,6 +50,9 @@ struct BatchRun {
     int vec = 1, threads = 256, max_nphase = 1, nt = 0, storage = 0;
     int map = 0;    // XCD-aware tile order
     int chunk = 0;  // tiles per XCD when map is set
+    Step2Batch pair;     // two steps per pass
+    int pair_chunk = 0;  // its tiles per XCD; the table lies behind the single step's
+    bool single = false; // every step its own launch, in the shape the caller set
     char *ws = nullptr;
     BatchLayout lay{};
     hipStream_t stream = nullptr, cap = nullptr;  // cap is owned (destroyed with the run)
@@ -80,10 +83,43 @@ mrtlbm_status upload_cells(BatchRun &B) {
     return e == hipSuccess ? MRTLBM_OK : hip_fail(e, "batch cell table upload");
 }
 
+// tiles of two steps per pass, appended to the single step's where the batch
+// takes them and the table has room (it is sized for single steps in the
+// smallest tiles)
+template <typename real>
+void add_pair_tiles(BatchRun &B, std::vector<int4> &tiles) {
+    B.pair = Step2Batch();
+    if (B.single || B.active.empty()) return;
+    std::vector<Step2Extent> ext;
+    for (int a : B.active) {
+        const mrtlbm_medium *m = B.cells[a];
+        if (!step2_takes<real>(make_cell<real>(m, m->cur))) return;
+        ext.push_back(Step2Extent{m->nx, m->ny, m->nz, m->nphase, m->gaxis});
+    }
+    const Step2Batch g = step2_batch_shape<real>(ext.data(), (int)ext.size());
+    if (!g.vec) return;
+    std::vector<int4> t;
+    for (size_t i = 0; i < ext.size(); i++) {
+        const Step2Extent &c = ext[i];
+        const int tr = step2_batch_rows<real>(g, c), nchunks = (c.nz + g.planes - 1) / g.planes;
+        for (int k = 0; k < nchunks; k++) {
+            const int z0 = (int)((long long)k * c.nz / nchunks), z1 = (int)((long long)(k + 1) * c.nz / nchunks);
+            for (int y0 = 0; y0 < c.ny; y0 += tr)
+                t.push_back(int4{B.active[i], y0, z0, std::min(tr, c.ny - y0) | (z1 - z0) << 16});
+        }
+    }
+    while (t.size() % 8) t.push_back(int4{B.active[0], 0, 0, 0});
+    if ((long long)(tiles.size() + t.size()) > B.lay.max_tiles) return;
+    tiles.insert(tiles.end(), t.begin(), t.end());
+    B.pair = g;
+    B.pair_chunk = (int)(t.size() / 8);
+}
+
 // tiles of the active cells (contiguous per cell) and per-cell tile ranges.
 // A tile is (cell, z, y0, rows): `rows` whole rows from y0, packed over the
 // block's threads; a row longer than the block is cut into x-chunks of one
 // tile each, (cell, z, y, -1 - chunk).
+template <typename real>
 mrtlbm_status upload_tiles(BatchRun &B) {
     std::vector<int4> tiles;
     std::vector<int> start;
@@ -110,7 +146,8 @@ mrtlbm_status upload_tiles(BatchRun &B) {
         B.chunk = (int)(tiles.size() / 8);
     }
     B.ntiles = (int)tiles.size();
-    if ((long long)B.ntiles > B.lay.max_tiles) return fail(MRTLBM_E_WORKSPACE, "tile table overflow");
+    add_pair_tiles<real>(B, tiles);
+    if ((long long)tiles.size() > B.lay.max_tiles) return fail(MRTLBM_E_WORKSPACE, "tile table overflow");
     hipError_t e = hipMemcpyAsync(B.ws + B.lay.tiles, tiles.data(), tiles.size() * sizeof(int4), hipMemcpyHostToDevice,
                                   B.stream);
     if (e == hipSuccess)
@@ -130,9 +167,14 @@ mrtlbm_status build_graph(BatchRun &B, int K) {
     double *finals = (double *)(B.ws + B.lay.finals);
     hipError_t e = hipStreamBeginCapture(B.cap, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
-    for (int i = 0; i < K && e == hipSuccess; i++)
-        e = launch_batch<real>(cells, tiles, B.ntiles, B.vec, B.threads, B.max_nphase, i & 1, i == K - 1, B.nt,
-                               B.chunk, B.storage, partials, B.cap);
+    // an even number of pairs: the buffers have changed places an even number
+    // of times after the block, and the graph can be replayed
+    const int pairs = B.pair.vec ? (K - 1) / 4 * 2 : 0;
+    for (int i = 0; i < pairs && e == hipSuccess; i++)
+        e = launch_batch2<real>(cells, tiles + B.ntiles, B.pair_chunk, B.pair, i & 1, B.cap);
+    for (int i = 0; i < K - 2 * pairs && e == hipSuccess; i++)
+        e = launch_batch<real>(cells, tiles, B.ntiles, B.vec, B.threads, B.max_nphase, i & 1, i == K - 2 * pairs - 1,
+                               B.nt, B.chunk, B.storage, partials, B.cap);
     if (e == hipSuccess) e = launch_batch_reduce(partials, start, (int)B.active.size(), finals, B.cap);
     if (e == hipSuccess)
         e = hipMemcpyAsync(B.pinned, finals, B.active.size() * NRED * sizeof(double), hipMemcpyDeviceToHost, B.cap);
@@ -164,7 +206,7 @@ mrtlbm_status run(BatchRun &B, double tol, mrtlbm_tol_kind kind, long long max_s
     bool rebuild = true;
     while (!B.active.empty()) {
         if (rebuild) {
-            st = upload_tiles(B);
+            st = upload_tiles<real>(B);
             if (st == MRTLBM_OK) st = build_graph<real>(B, K);
             if (st != MRTLBM_OK) return st;
             rebuild = false;
@@ -232,6 +274,7 @@ static mrtlbm_status prepare(BatchRun &B, mrtlbm_medium *const *cells, int n, vo
     B.nt = m0->launch.nt;
     B.map = m0->launch.map;
     B.storage = m0->storage;
+    B.single = m0->single;
     B.ws = (char *)workspace_dev;
     B.lay = lay;
     B.stream = m0->stream;
@@ -246,7 +289,7 @@ template <typename real>
 static mrtlbm_status time_batch(BatchRun &B, int steps, double *ms) {
     if (B.active.empty()) return fail(MRTLBM_E_ARG, "no cells to time");
     mrtlbm_status st = upload_cells<real>(B);
-    if (st == MRTLBM_OK) st = upload_tiles(B);
+    if (st == MRTLBM_OK) st = upload_tiles<real>(B);
     if (st != MRTLBM_OK) return st;
     const Cell<real> *cells = (const Cell<real> *)(B.ws + B.lay.cells);
     const int4 *tiles = (const int4 *)(B.ws + B.lay.tiles);
@@ -297,6 +340,7 @@ extern "C" mrtlbm_status mrtlbm_batch_autotune(mrtlbm_medium *const *cells, int 
     BatchRun B;
     mrtlbm_status st = prepare(B, cells, n, workspace_dev, workspace_bytes, false);
     if (st != MRTLBM_OK) return st;
+    B.single = true;  // the shape is the single step's
     for (int i = 0; i < n; i++) {
         st = mrtlbm_init(cells[i], nullptr, 0);
         if (st != MRTLBM_OK) return st;
@@ -329,6 +373,7 @@ extern "C" mrtlbm_status mrtlbm_batch_autotune(mrtlbm_medium *const *cells, int 
     mrtlbm_medium *m0 = cells[0];
     const int bx = std::min(bt, 64);
     m0->launch = Launch{bv, bx, bt / bx, bn, bm};
+    m0->single = false;
     drop_graphs(m0);
     for (int i = 0; i < n; i++) {
         cells[i]->initialised = false;

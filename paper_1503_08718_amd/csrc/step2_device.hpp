@@ -17,7 +17,8 @@
 //
 // Per step, single -> two per pass (MI355X): FP32 256^3 95.6 -> 55.2 us, 192^3
 // 39.2 -> 25.6, 128^3 12.9 -> 10.5, 75 x 61 x 87 8.8 -> 5.6; FP64 256^3 195.5 ->
-// 106.6, 128^3 21.6 -> 13.4.  What bounds it now is the arithmetic (57 vector
+// 106.6, 128^3 21.6 -> 13.4; batches in FP32, 24 solves of 64..128 per axis
+// 136 -> 84, 32 of 32..64 29.8 -> 22.0, 9 unit cells of 56 x 56 28.7 -> 18.2.  What bounds it now is the arithmetic (57 vector
 // instructions per node and step, 63 of 110 us at 256^3) together with the
 // 553 MB that two steps still move (5.0 TB/s; a four-array copy reaches 5.1).
 // Registers decide the layout: the planes of a vector of 4 leave 128 per wave

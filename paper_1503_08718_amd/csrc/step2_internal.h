@@ -28,4 +28,31 @@ Step2Shape step2_shape(int nx, int ny, int nz, int nphase);
 template <typename real>
 hipError_t launch_step2(const Cell<real> &c, const Step2Shape &g, hipStream_t s);
 
+// The same for many cells in one launch.  tiles: int4 (cell, first row, first
+// plane, rows | planes << 16), one block each, rows = 0: an empty tile; the
+// table holds 8 * chunk tiles and block b takes tile (b % 8) * chunk + b / 8.
+struct Step2Batch {
+    int vec = 0;       // 0: the batch takes single steps
+    int threads = 0, planes = 0;
+    bool ragged = false;
+    int gaxis = 0;     // the cells' gradient axis
+    size_t lds = 0, state_bytes = 0;
+};
+
+struct Step2Extent {
+    int nx, ny, nz, nphase, gaxis;
+};
+
+// the fastest block size and chunk length for these cells by the model
+template <typename real>
+Step2Batch step2_batch_shape(const Step2Extent *cells, int n);
+
+// rows of a cell's tiles under that shape
+template <typename real>
+int step2_batch_rows(const Step2Batch &g, const Step2Extent &c);
+
+template <typename real>
+hipError_t launch_batch2(const Cell<real> *cells, const int4 *tiles, int chunk, const Step2Batch &g, int parity,
+                         hipStream_t s);
+
 }  // namespace mrt

@@ -1,8 +1,9 @@
-// The two-steps-per-pass kernel (step2_device.hpp) for one cell, and how a
-// cell is cut into blocks for it.
+// The two-steps-per-pass kernels (step2_device.hpp) for one cell and for many,
+// and how cells are cut into blocks for them.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "step2_device.hpp"
 #include "step2_internal.h"
@@ -141,10 +142,139 @@ hipError_t launch_step2(const Cell<real> &c, const Step2Shape &g, hipStream_t s)
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// many cells
+// ---------------------------------------------------------------------------
+
+template <typename real, int VEC, bool RAG, int NT, int GA>
+__global__ void __launch_bounds__((step2_max_threads<real, VEC>()))
+k_batch2(const Cell<real> *__restrict__ cells, const int4 *__restrict__ tiles, int parity, int chunk) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int4 tile = tiles[(int)(blockIdx.x % 8u) * chunk + (int)(blockIdx.x / 8u)];
+    const int rows = tile.w & 0xffff, planes = tile.w >> 16;
+    if (rows == 0) return;
+    Cell<real> c = cells[tile.x];
+    if (parity) {
+        const real *t = c.src;
+        c.src = c.dst;
+        c.dst = const_cast<real *>(t);
+    }
+    march2<real, VEC, RAG, NT, GA>(c, reinterpret_cast<real *>(smem_raw), rows, tile.y, rows, tile.z, planes);
+}
+
+template <typename real>
+int step2_batch_rows(const Step2Batch &g, const Step2Extent &c) {
+    const int rpw = 64 / ((c.nx + g.vec - 1) / g.vec);
+    const int tr = std::min(g.threads / 64 * rpw - 4, c.ny);
+    if (tr < 1) return 0;
+    const int ntiles = (c.ny + tr - 1) / tr;
+    return (c.ny + ntiles - 1) / ntiles;
+}
+
+template <typename real>
+Step2Batch step2_batch_shape(const Step2Extent *cells, int n) {
+    Step2Batch g;
+    int vec = 0;
+    double nodes = 0;
+    for (int i = 0; i < n; i++) vec = std::max(vec, step2_vec(sizeof(real), cells[i].nx));
+    g.gaxis = cells[0].gaxis;
+    for (int i = 0; i < n; i++) {
+        const Step2Extent &c = cells[i];
+        const long long N = (long long)c.nx * c.ny * c.nz;
+        // as for one cell; and one gradient axis, which the kernel is built for
+        if (c.nx < vec || c.nx > 64 * vec || c.ny < 2 || c.nz < 2 || N >= (1LL << 31) ||
+            (long long)c.nx * c.ny >= (1LL << 28) || c.gaxis != g.gaxis)
+            return Step2Batch();
+        g.ragged = g.ragged || c.nx % vec != 0;
+        nodes += (double)N;
+    }
+    g.state_bytes = (size_t)(8.0 * sizeof(real) * nodes);
+    const int maxw = (sizeof(real) * vec > 16 ? 512 : 1024) / 64;
+    const double per_wave = sizeof(real) == 8 && vec == 2 ? 0.48 : 0.84;
+    double tmin = 2.0 * (2.4 + (sizeof(real) == 4 ? 5.5 : 9.0) * 1e-6 * nodes);
+    Step2Batch best;
+    g.vec = vec;
+    for (int w = 1; w <= maxw; w++) {
+        g.threads = 64 * w;
+        g.lds = 0;
+        bool ok = true;
+        for (int i = 0; i < n && ok; i++) {
+            const int tr = step2_batch_rows<real>(g, cells[i]);
+            ok = tr > 0;
+            const int len = (cells[i].nx + vec - 1) / vec * vec;
+            if (ok) g.lds = std::max(g.lds, sizeof(real) * (size_t)step2_lds_reals(tr, len, cells[i].nphase));
+        }
+        if (!ok || g.lds > (size_t)STEP2_LDS) continue;
+        const int occ = std::min(maxw / w, (int)(STEP2_LDS / g.lds));
+        for (int planes : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64}) {
+            double blocks = 0;
+            for (int i = 0; i < n; i++) {
+                const int tr = step2_batch_rows<real>(g, cells[i]);
+                blocks += (double)((cells[i].ny + tr - 1) / tr) * ((cells[i].nz + planes - 1) / planes);
+            }
+            const double k = std::min((double)occ, std::ceil(blocks / STEP2_CUS));
+            double work = 0, longest = 0;
+            for (int i = 0; i < n; i++) {
+                const Step2Extent &c = cells[i];
+                const int tr = step2_batch_rows<real>(g, c), rpw = 64 / ((c.nx + vec - 1) / vec);
+                const int nchunks = (c.nz + planes - 1) / planes, per = (c.nz + nchunks - 1) / nchunks;
+                const double t = 7.0 + (per + 1) * (per_wave * (tr + 1.0) / rpw * k / 4.0 + 0.45);
+                work += t * ((c.ny + tr - 1) / tr) * nchunks;
+                longest = std::max(longest, t);
+            }
+            // blocks start as others end: half of the longest one is lost at the end
+            const double t = std::max(longest, work / (STEP2_CUS * k) + (blocks > STEP2_CUS * k ? 0.5 * longest : 0.0));
+            if (t < tmin) {
+                tmin = t;
+                g.planes = planes;
+                best = g;
+            }
+        }
+    }
+    return best;
+}
+
+template <typename real, int VEC, bool RAG, int GA>
+static void launch_batch2_a(const Cell<real> *cells, const int4 *tiles, int chunk, const Step2Batch &g, int parity,
+                            hipStream_t s) {
+    const dim3 grid((unsigned)(8 * chunk)), block(g.threads);
+    if (g.state_bytes > STEP2_CACHE)
+        hipLaunchKernelGGL((k_batch2<real, VEC, RAG, 2, GA>), grid, block, g.lds, s, cells, tiles, parity, chunk);
+    else
+        hipLaunchKernelGGL((k_batch2<real, VEC, RAG, 0, GA>), grid, block, g.lds, s, cells, tiles, parity, chunk);
+}
+
+template <typename real, int VEC, bool RAG>
+static void launch_batch2_v(const Cell<real> *cells, const int4 *tiles, int chunk, const Step2Batch &g, int parity,
+                            hipStream_t s) {
+    if (g.gaxis == 0) launch_batch2_a<real, VEC, RAG, 0>(cells, tiles, chunk, g, parity, s);
+    else if (g.gaxis == 1) launch_batch2_a<real, VEC, RAG, 1>(cells, tiles, chunk, g, parity, s);
+    else launch_batch2_a<real, VEC, RAG, 2>(cells, tiles, chunk, g, parity, s);
+}
+
+template <typename real>
+hipError_t launch_batch2(const Cell<real> *cells, const int4 *tiles, int chunk, const Step2Batch &g, int parity,
+                         hipStream_t s) {
+    if constexpr (sizeof(real) == 4) {
+        if (g.ragged) launch_batch2_v<real, 4, true>(cells, tiles, chunk, g, parity, s);
+        else launch_batch2_v<real, 4, false>(cells, tiles, chunk, g, parity, s);
+    } else if (g.vec == 2) {
+        if (g.ragged) launch_batch2_v<real, 2, true>(cells, tiles, chunk, g, parity, s);
+        else launch_batch2_v<real, 2, false>(cells, tiles, chunk, g, parity, s);
+    } else {
+        if (g.ragged) launch_batch2_v<real, 4, true>(cells, tiles, chunk, g, parity, s);
+        else launch_batch2_v<real, 4, false>(cells, tiles, chunk, g, parity, s);
+    }
+    return hipGetLastError();
+}
+
 #define MRT_INST2(real)                                                                                            \
     template bool step2_takes<real>(const Cell<real> &);                                                           \
     template Step2Shape step2_shape<real>(int, int, int, int);                                                     \
-    template hipError_t launch_step2<real>(const Cell<real> &, const Step2Shape &, hipStream_t);
+    template hipError_t launch_step2<real>(const Cell<real> &, const Step2Shape &, hipStream_t);                   \
+    template Step2Batch step2_batch_shape<real>(const Step2Extent *, int);                                         \
+    template int step2_batch_rows<real>(const Step2Batch &, const Step2Extent &);                                  \
+    template hipError_t launch_batch2<real>(const Cell<real> *, const int4 *, int, const Step2Batch &, int, hipStream_t);
 MRT_INST2(float)
 MRT_INST2(double)
 
