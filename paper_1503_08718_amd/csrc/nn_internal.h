@@ -13,12 +13,23 @@ struct ConvGeom {
 };
 hipError_t nn_conv_fwd(const void *in, const void *w, const float *bias, const ConvGeom &g, int relu, void *out,
                        float *out_f32, hipStream_t s);
+// the kernel with activations staged in LDS (nn_conv.hip): channel counts and
+// alignments it takes, and its launch
+bool nn_conv_tile_takes(const void *in, const void *w, const ConvGeom &g, const void *out, const void *out_f32);
+hipError_t nn_conv_tile(const void *in, const void *w, const float *bias, const ConvGeom &g, int relu, void *out,
+                        float *out_f32, hipStream_t s);
 hipError_t nn_weight_flip(const void *w, int cin, int cout, int kpad, int kpad_t, void *wt, hipStream_t s);
 int nn_wgrad_splits(const ConvGeom &g);
 int nn_wgrad_partials(const ConvGeom &g);
 hipError_t nn_conv_wgrad(const void *x, const void *dy, const ConvGeom &g, int splits, float *partials, float *dw,
                          hipStream_t s);
 hipError_t nn_bias_grad(const void *dy, long long nvox, int c, int splits, float *partials, float *db, hipStream_t s);
+// the same from tiles staged in LDS (nn_wgrad.hip), with the bias gradient (db
+// may be NULL): cin it takes, splits (partials of cout * (kpad + 1) floats each)
+bool nn_wgrad_tile_takes(const ConvGeom &g);
+int nn_wgrad_tile_splits(const ConvGeom &g);
+hipError_t nn_wgrad_tile(const void *x, const void *dy, const ConvGeom &g, float *partials, float *dw, float *db,
+                         hipStream_t s);
 hipError_t nn_relu_bwd(const void *y, const void *dy, void *dx, long long n, hipStream_t s);
 hipError_t nn_add(const void *a, const void *b, void *out, long long n, hipStream_t s);
 hipError_t nn_pool2(int fwd, const void *in, int n, int D, int H, int W, int c, void *out, hipStream_t s);

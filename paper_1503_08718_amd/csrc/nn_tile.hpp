@@ -1,0 +1,62 @@
+// Spatial tiles of the 3x3x3 convolutions: a block stages the activations of
+// an 8 x TY x TZ tile of voxels and its halo in LDS once, and every tap reads
+// them from there.
+#pragma once
+
+#include "nn_device.hpp"
+
+namespace mrt {
+
+constexpr int TILE_X = 8;
+
+template <int TY, int TZ>
+struct Tile {
+    static constexpr int HX = TILE_X + 2, HY = TY + 2, HZ = TZ + 2;
+    static constexpr int HALO = HX * HY * HZ;  // voxels staged
+
+    // tile t of the launch: sample and first voxel
+    int nb, x0, y0, z0;
+
+    __device__ __forceinline__ Tile(const ConvGeom &g, unsigned t) {
+        const unsigned ntx = (g.W + TILE_X - 1) / TILE_X, nty = (g.H + TY - 1) / TY, ntz = (g.D + TZ - 1) / TZ;
+        x0 = (int)(t % ntx) * TILE_X;
+        t /= ntx;
+        y0 = (int)(t % nty) * TY;
+        t /= nty;
+        z0 = (int)(t % ntz) * TZ;
+        nb = (int)(t / ntz);
+    }
+
+    // voxel of the input under halo position h, -1 in zero padding; positions
+    // further outside (partial tiles) are not used and give any voxel
+    __device__ __forceinline__ int source(const ConvGeom &g, int h) const {
+        int x = x0 + h % HX - 1, y = y0 + (h / HX) % HY - 1, z = z0 + h / (HX * HY) - 1;
+        const bool ox = x < 0 || x >= g.W, oy = y < 0 || y >= g.H, oz = z < 0 || z >= g.D;
+        x = x < 0 ? g.W - 1 : (x >= g.W ? 0 : x);
+        y = y < 0 ? g.H - 1 : (y >= g.H ? 0 : y);
+        z = z < 0 ? g.D - 1 : (z >= g.D ? 0 : z);
+        const bool ok = (!ox || (g.circ & 1)) && (!oy || (g.circ & 2)) && (!oz || (g.circ & 4));
+        return ok ? ((nb * g.D + z) * g.H + y) * g.W + x : -1;
+    }
+
+    // voxel v (0 .. 8 TY TZ - 1) of the tile, -1 outside the volume
+    __device__ __forceinline__ int inside(const ConvGeom &g, int v) const {
+        const int x = x0 + v % TILE_X, y = y0 + v / TILE_X % TY, z = z0 + v / (TILE_X * TY);
+        return x < g.W && y < g.H && z < g.D ? ((nb * g.D + z) * g.H + y) * g.W + x : -1;
+    }
+    __device__ __forceinline__ bool partial(const ConvGeom &g) const {
+        return x0 + TILE_X > g.W || y0 + TY > g.H || z0 + TZ > g.D;
+    }
+};
+
+inline long long tile_count(const ConvGeom &g, int ty, int tz) {
+    return (long long)g.n * ((g.D + tz - 1) / tz) * ((g.H + ty - 1) / ty) * ((g.W + TILE_X - 1) / TILE_X);
+}
+
+// a tap's offset in halo positions
+template <int TY, int TZ>
+__host__ __device__ constexpr int tap_shift(int tap) {
+    return (tap / 9) * Tile<TY, TZ>::HX * Tile<TY, TZ>::HY + (tap / 3) % 3 * Tile<TY, TZ>::HX + tap % 3;
+}
+
+}  // namespace mrt
