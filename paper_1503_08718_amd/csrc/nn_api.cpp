@@ -59,9 +59,10 @@ extern "C" mrtlbm_status mrtlbm_nn_conv3d_dgrad(const void *dout, int n, int d, 
 extern "C" size_t mrtlbm_nn_wgrad_scratch_bytes(int n, int d, int h, int w, int cin, int cout) {
     ConvGeom g;
     if (!geom(n, d, h, w, cin, cout, 0, &g)) return 0;
+    const size_t t = nn_wgrad_tile_takes(g) ? (size_t)nn_wgrad_tile_splits(g) * (size_t)cout * (g.kpad + 1) * sizeof(float) : 0;
     const size_t a = (size_t)nn_wgrad_partials(g) * (size_t)cout * g.kpad * sizeof(float);
     const size_t b = (size_t)nn_wgrad_splits(g) * (size_t)cout * sizeof(float);
-    return a > b ? a : b;
+    return std::max(t, std::max(a, b));
 }
 
 extern "C" mrtlbm_status mrtlbm_nn_conv3d_wgrad(const void *in, const void *dout, int n, int d, int h, int w, int cin,
@@ -72,6 +73,9 @@ extern "C" mrtlbm_status mrtlbm_nn_conv3d_wgrad(const void *in, const void *dout
         return fail(MRTLBM_E_ARG, "conv3d_wgrad: bad arguments");
     if (cout > 128) return fail(MRTLBM_E_ARG, "conv3d_wgrad: cout %d > 128", cout);
     hipStream_t s = (hipStream_t)stream;
+    // 16-byte accesses to the activations, the scratch and four sums at a time
+    const bool aligned = (((uintptr_t)in | (uintptr_t)dout | (uintptr_t)scratch) & 15) == 0;
+    if (aligned && nn_wgrad_tile_takes(g)) return ret(nn_wgrad_tile(in, dout, g, scratch, dw, db, s), "conv3d_wgrad");
     const int splits = nn_wgrad_splits(g);
     hipError_t e = nn_conv_wgrad(in, dout, g, splits, scratch, dw, s);
     if (e == hipSuccess && db) e = nn_bias_grad(dout, (long long)n * d * h * w, cout, splits, scratch, db, s);
