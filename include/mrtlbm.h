@@ -255,9 +255,9 @@ mrtlbm_status mrtlbm_state_set(mrtlbm_medium *m, const void *f_dev, long long st
 mrtlbm_status mrtlbm_info(const mrtlbm_medium *m, double *scale, long long *steps, mrtlbm_launch *launch);
 
 /* Choose the step kernel's block shape.  NULL restores the default.  A shape
- * set here is used for every step; otherwise moment storage takes two steps
- * per pass over memory where that is faster (same results bit for bit), and
- * the default, tuned or loaded shape serves the remaining single steps. */
+ * set here is used for every step; otherwise a launch takes several steps
+ * where that is faster and the storage allows it (same results bit for bit),
+ * and the default, tuned or loaded shape serves the remaining single steps. */
 mrtlbm_status mrtlbm_set_launch(mrtlbm_medium *m, const mrtlbm_launch *launch);
 
 /* Time every admissible block shape on this medium (hip events, a few

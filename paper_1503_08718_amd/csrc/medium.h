@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "../../include/mrtlbm.h"
+#include "box_internal.h"
 #include "lbm_internal.h"
 #include "step2_internal.h"
 
@@ -71,6 +72,7 @@ struct mrtlbm_medium {
     bool initialised = false;
     mrt::Launch launch{4, 64, 4, 0, 0};
     mrt::Step2Shape pair;      // how two steps per pass are cut into blocks
+    mrt::BoxShape box;         // small cells: several steps per launch
     bool single = false;       // every step its own launch, in the shape the caller set
     std::vector<mrt::GraphEntry> graphs;
 };

@@ -1,5 +1,6 @@
-"""Two time steps per pass over memory (moment storage): bit for bit the same
-as single steps, which a caller-set block shape selects, and on the oracle."""
+"""Several time steps per launch (pairs over large cells, more over small
+ones): bit for bit the same as single steps, which a caller-set block shape
+selects, and on the oracle."""
 
 import numpy as np
 import pytest
@@ -108,3 +109,27 @@ def test_batched_pairs_equal_single_steps(api, axis, shapes, prec):
         h.step(30)
         assert r["steps"] == 30
         assert torch.equal(g.state_get(), h.state_get())
+
+
+@pytest.mark.parametrize("prec,storage", [("f32", "moments"), ("f64", "moments"), ("f64", "populations")])
+@pytest.mark.parametrize("shape", [(1, 9, 7), (5, 2, 3), (7, 16, 20), (16, 16, 16), (24, 40, 30), (32, 32, 32), (64, 9, 8)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_small_cells_equal_single_steps(api, shape, prec, storage):
+    """Every mix of walls; step counts that end on full and on shorter
+    launches; a solve's replayed graph against plain steps."""
+    import torch
+
+    m, T0 = _media(shape, sum(shape))
+    for axis, sides in WALLS:
+        g = api.Medium(m.phase, m.k, precision=prec, storage=storage)
+        h = api.Medium(m.phase, m.k, precision=prec, storage=storage)
+        h.set_launch(*h.info()["launch"])
+        for steps in (2, 7, 13):
+            for c in (g, h):
+                c.set_bc(axis, 0.8, -0.4, sides).init(T0, flux=True)
+                c.step(steps)
+            assert torch.equal(g.state_get(), h.state_get()), (axis, sides, steps)
+        g.init(T0, flux=True)
+        g.solve(1e-30, "keff", 30, check_every=10)
+        h.init(T0, flux=True).step(30)
+        assert torch.equal(g.state_get(), h.state_get()), (axis, sides)
