@@ -12,14 +12,24 @@
 // L1, which bound it.  The products and their order (tap, then channel, in
 // chunks of 32) are those of k_conv_fwd: the results agree bit for bit.
 //
-// Gathered -> staged (MI355X): 16 -> 16 channels on 64^3 voxels 26.8 -> 15.8 us,
-// on 4 x 64^3 89 -> 46; 32 -> 16 on 64^3 53.7 -> 20.4; 64 -> 64 on 16^3 29.8 -> 12.0;
-// 128 -> 128 on 8^3 38.1 -> 20; one inference of a 128^3 cell 0.58 -> 0.36 ms.
+// Gathered -> staged (MI355X): 16 -> 16 channels on 64^3 voxels 26.8 -> 15.4 us,
+// on 4 x 64^3 89 -> 42; 32 -> 16 on 64^3 53.7 -> 18.6; 64 -> 64 on 16^3 29.8 -> 12.0;
+// 128 -> 128 on 8^3 38.1 -> 20; one inference of a 128^3 cell 0.58 -> 0.33 ms.
 // LDS reads (one per product at 16 output channels) and, on the coarse
 // levels, the chain of 54 or 108 dependent products bound it now.
 #include "nn_tile.hpp"
 
 namespace mrt {
+
+// positions of a plane of 8 channels, a zero vector behind its voxels.  The
+// large tile's planes lie a multiple of 16 apart, as neighbouring quarters of
+// a wave read neighbouring ones; the small tiles, where the LDS is not what a
+// launch waits for, gain nothing from that (64 -> 64 on 16^3 10.8 us, 11.1 with it)
+template <int TY, int TZ>
+constexpr int conv_plane() {
+    typedef Tile<TY, TZ> T;
+    return TY == 8 ? T::SPAN / 16 * 16 + 16 : T::SPAN + 1;
+}
 
 template <int CIN, int MT, int NT>
 __global__ void __launch_bounds__(256) k_conv_tile(const bf16 *__restrict__ in, const bf16 *__restrict__ w,
@@ -27,7 +37,7 @@ __global__ void __launch_bounds__(256) k_conv_tile(const bf16 *__restrict__ in, 
                                                    bf16 *__restrict__ out, float *__restrict__ out_f32) {
     constexpr int TY = MT == 4 ? 8 : 4, TZ = MT == 1 ? 2 : 4;
     typedef Tile<TY, TZ> T;
-    constexpr int GROUPS = CIN / 8, PLANE = T::HALO + 1;  // a plane of 8 channels ends with a zero vector
+    constexpr int GROUPS = CIN / 8, PLANE = conv_plane<TY, TZ>(), PITCH = T::PITCH;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     bf16x8 *lds = reinterpret_cast<bf16x8 *>(smem_raw);
     const T tile(g, blockIdx.x);
@@ -66,21 +76,21 @@ __global__ void __launch_bounds__(256) k_conv_tile(const bf16 *__restrict__ in, 
 #pragma unroll
         for (int u = 0; u < BATCH; u++) {
             const int i = (i0 + u) * 256 + threadIdx.x;
-            if (i < ITEMS) lds[i % GROUPS * PLANE + i / GROUPS] = v[u];
+            if (i < ITEMS) lds[i % GROUPS * PLANE + T::place(i / GROUPS)] = v[u];
         }
     }
-    if (threadIdx.x < GROUPS) lds[threadIdx.x * PLANE + T::HALO] = zero8();
+    if (threadIdx.x < GROUPS) lds[threadIdx.x * PLANE + T::SPAN] = zero8();
     __syncthreads();
 
     int pos[MT];  // halo position of this lane's voxel of each group, for the first tap
     int vx[MT], vy[MT], vz[MT];
 #pragma unroll
     for (int i = 0; i < MT; i++) {
-        const int m = (wave * MT + i) * 16 + (lane & 15);
-        vx[i] = m % TILE_X;
-        vy[i] = m / TILE_X % TY;
-        vz[i] = m / (TILE_X * TY);
-        pos[i] = (vz[i] * T::HY + vy[i]) * T::HX + vx[i];
+        const int l = T::line(wave * MT + i, (lane >> 3) & 1);
+        vx[i] = lane & 7;
+        vy[i] = l % TY;
+        vz[i] = l / TY;
+        pos[i] = (vz[i] * T::HY + vy[i]) * PITCH + vx[i];
     }
     f32x4 acc[MT][NT];
 #pragma unroll
@@ -102,7 +112,7 @@ __global__ void __launch_bounds__(256) k_conv_tile(const bf16 *__restrict__ in, 
                     a[j][q] = wk[j][q];
                     wk[j][q] = *reinterpret_cast<const bf16x8 *>(wrow[j] + next + q * 32);
                 }
-            const bf16x8 *at = base + (row / 3) * T::HX * T::HY + row % 3 * T::HX;
+            const bf16x8 *at = base + (row / 3 * T::HY + row % 3) * PITCH;
 #pragma unroll
             for (int q = 0; q < CHUNKS; q++) {
                 const int dx = q / (CIN / 32), c = q % (CIN / 32);
@@ -129,12 +139,12 @@ __global__ void __launch_bounds__(256) k_conv_tile(const bf16 *__restrict__ in, 
 #pragma unroll
             for (int u = 0; u < TPC; u++)
                 if (sub == u) {
-                    shift = q * TPC + u < 27 ? tap_shift<TY, TZ>(q * TPC + u) : 0;
+                    shift = q * TPC + u < 27 ? T::tap(q * TPC + u) : 0;
                     pad = q * TPC + u >= 27;
                 }
             bf16x8 b[MT];
 #pragma unroll
-            for (int i = 0; i < MT; i++) b[i] = base[pad ? T::HALO : pos[i] + shift];
+            for (int i = 0; i < MT; i++) b[i] = base[pad ? T::SPAN : pos[i] + shift];
 #pragma unroll
             for (int i = 0; i < MT; i++)
 #pragma unroll
@@ -175,7 +185,7 @@ static hipError_t launch_tile(const bf16 *in, const bf16 *w, const float *bias, 
                               float *out_f32, hipStream_t s) {
     constexpr int TY = MT == 4 ? 8 : 4, TZ = MT == 1 ? 2 : 4;
     const dim3 grid((unsigned)tile_count(g, TY, TZ), g.cout / (16 * NT));
-    const size_t lds = (size_t)(Tile<TY, TZ>::HALO + 1) * CIN * sizeof(bf16);
+    const size_t lds = (size_t)conv_plane<TY, TZ>() * CIN * sizeof(bf16);
     hipLaunchKernelGGL((k_conv_tile<CIN, MT, NT>), grid, dim3(256), lds, s, in, w, bias, g, relu, out, out_f32);
     return hipGetLastError();
 }

@@ -12,6 +12,7 @@
 // gradient axis).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "nn_device.hpp"
@@ -110,9 +111,9 @@ __global__ void __launch_bounds__(256) k_conv_fwd(const bf16 *__restrict__ in, c
 
 // weights of the adjoint convolution: wt[ci][flip(tap) * cout + co] = w[co][tap * cin + ci]
 __global__ void k_weight_flip(const bf16 *__restrict__ w, int cin, int cout, int kpad, int kpad_t, bf16 *__restrict__ wt) {
-    const long long total = (long long)cin * kpad_t;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total; i += (long long)gridDim.x * blockDim.x) {
-        const int ci = (int)(i / kpad_t), kt = (int)(i % kpad_t);
+    const unsigned total = (unsigned)cin * (unsigned)kpad_t;
+    for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+        const int ci = (int)(i / (unsigned)kpad_t), kt = (int)(i - (unsigned)ci * (unsigned)kpad_t);
         bf16 val = (bf16)0.0f;
         if (kt < 27 * cout) {
             const int tapt = kt / cout, co = kt % cout;
@@ -381,6 +382,27 @@ __global__ void k_pool2_bwd(const bf16 *__restrict__ dout, int n, int D, int H, 
     }
 }
 
+// the same on 8 channels (16 bytes) per thread, c8 = c / 8 groups per voxel,
+// fewer than 2^31 groups: 32-bit index arithmetic, since the 64-bit divisions
+// of one channel per thread take longer than the voxel's memory traffic
+__global__ void k_pool2_bwd8(const bf16x8 *__restrict__ dout, int n, int D, int H, int W, int c8, bf16x8 *__restrict__ din) {
+    const unsigned total = (unsigned)n * D * H * W * c8;
+    const unsigned Do = D / 2, Ho = H / 2, Wo = W / 2;
+    for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+        unsigned r = i / c8;
+        const unsigned cg = i - r * c8, x = r % W;
+        r /= W;
+        const unsigned y = r % H;
+        r /= H;
+        const unsigned z = r % D, nb = r / D;
+        const bf16x8 v = dout[(((nb * Do + z / 2) * Ho + y / 2) * Wo + x / 2) * c8 + cg];
+        bf16x8 o;
+#pragma unroll
+        for (int e = 0; e < 8; e++) o[e] = (bf16)((float)v[e] * 0.125f);
+        din[i] = o;
+    }
+}
+
 // nearest 2x upsampling; (D, H, W) are the input extents
 __global__ void k_up2_fwd(const bf16 *__restrict__ in, int n, int D, int H, int W, int c, bf16 *__restrict__ out) {
     const int D2 = 2 * D, H2 = 2 * H, W2 = 2 * W;
@@ -396,18 +418,47 @@ __global__ void k_up2_fwd(const bf16 *__restrict__ in, int n, int D, int H, int 
     }
 }
 
-// k_up2_fwd on 8 channels per thread (c8 = c / 8 groups per voxel)
+// k_up2_fwd on 8 channels per thread (c8 = c / 8 groups per voxel, fewer than
+// 2^31 groups)
 __global__ void k_up2_fwd8(const bf16x8 *__restrict__ in, int n, int D, int H, int W, int c8, bf16x8 *__restrict__ out) {
-    const int D2 = 2 * D, H2 = 2 * H, W2 = 2 * W;
-    const long long total = (long long)n * D2 * H2 * W2 * c8;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total; i += (long long)gridDim.x * blockDim.x) {
-        const int cg = (int)(i % c8);
-        long long r = i / c8;
-        const int x = (int)(r % W2); r /= W2;
-        const int y = (int)(r % H2); r /= H2;
-        const int z = (int)(r % D2);
-        const long long nb = r / D2;
+    const unsigned D2 = 2 * D, H2 = 2 * H, W2 = 2 * W;
+    const unsigned total = (unsigned)n * D2 * H2 * W2 * c8;
+    for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+        unsigned r = i / c8;
+        const unsigned cg = i - r * c8, x = r % W2;
+        r /= W2;
+        const unsigned y = r % H2;
+        r /= H2;
+        const unsigned z = r % D2, nb = r / D2;
         out[i] = in[(((nb * D + z / 2) * H + y / 2) * W + x / 2) * c8 + cg];
+    }
+}
+
+// sums of 2 x 2 x 2 fine voxels, 8 channels per thread: the backward of
+// upsampling (scale 1, (D, H, W) the coarse extents) and average pooling
+// (scale 1/8), the eight values added in z, y, x order
+__global__ void k_sum2_8(const bf16x8 *__restrict__ fine, int n, int D, int H, int W, int c8, float scale,
+                         bf16x8 *__restrict__ out) {
+    const unsigned H2 = 2 * H, W2 = 2 * W, D2 = 2 * D, total = (unsigned)n * D * H * W * c8;
+    for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+        unsigned r = i / c8;
+        const unsigned cg = i - r * c8, x = r % W;
+        r /= W;
+        const unsigned y = r % H;
+        r /= H;
+        const unsigned z = r % D, nb = r / D;
+        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (unsigned d = 0; d < 8; d++) {
+            const bf16x8 v =
+                fine[(((nb * D2 + 2 * z + (d >> 2)) * H2 + 2 * y + (d >> 1 & 1)) * W2 + 2 * x + (d & 1)) * c8 + cg];
+#pragma unroll
+            for (int e = 0; e < 8; e++) acc[e] += (float)v[e];
+        }
+        bf16x8 o;
+#pragma unroll
+        for (int e = 0; e < 8; e++) o[e] = (bf16)(acc[e] * scale);
+        out[i] = o;
     }
 }
 
@@ -491,9 +542,11 @@ __global__ void k_features(const uint8_t *__restrict__ phase, int D, int H, int 
 // first fine index of coarse cell c when n fine voxels are resampled to nc:
 // fine voxel i belongs to the coarse cell that holds its centre, i.e. to
 // floor((2i + 1) nc / (2n)); the first i of cell c solves (2i + 1) nc >= 2 c n
+// (idx: unsigned where 2 (c + 1) n stays below 2^31)
+template <typename idx>
 __device__ __forceinline__ int box_lo(int c, int n, int nc) {
     const long long num = 2LL * c * n - nc;
-    return num <= 0 ? 0 : (int)((num + 2LL * nc - 1) / (2LL * nc));
+    return num <= 0 ? 0 : (int)((idx)(num + 2LL * nc - 1) / (idx)(2LL * nc));
 }
 
 // Network input on a coarse grid (Dc, Hc, Wc) for a medium of (D, H, W)
@@ -501,16 +554,16 @@ __device__ __forceinline__ int box_lo(int c, int n, int nc) {
 // centres lie in the coarse voxel (a coarse voxel with none, when the grid
 // is refined, takes the fine voxel under its centre), channel 6 is the
 // coarse voxel's own x coordinate, channel 7 is zero.
+template <typename idx>
 __global__ void k_features_resampled(const uint8_t *__restrict__ phase, int D, int H, int W,
                                      const float *__restrict__ feat, int Dc, int Hc, int Wc, bf16 *__restrict__ out) {
-    const long long total = (long long)Dc * Hc * Wc;
-    for (long long v = blockIdx.x * (long long)blockDim.x + threadIdx.x; v < total; v += (long long)gridDim.x * blockDim.x) {
-        const int cx = (int)(v % Wc);
-        const long long r = v / Wc;
-        const int cy = (int)(r % Hc), cz = (int)(r / Hc);
-        int x0 = box_lo(cx, W, Wc), x1 = box_lo(cx + 1, W, Wc);
-        int y0 = box_lo(cy, H, Hc), y1 = box_lo(cy + 1, H, Hc);
-        int z0 = box_lo(cz, D, Dc), z1 = box_lo(cz + 1, D, Dc);
+    const idx total = (idx)Dc * Hc * Wc;
+    for (idx v = (idx)blockIdx.x * blockDim.x + threadIdx.x; v < total; v += (idx)gridDim.x * blockDim.x) {
+        const idx r = v / Wc;
+        const int cx = (int)(v - r * Wc), cz = (int)(r / Hc), cy = (int)(r - (idx)cz * Hc);
+        int x0 = box_lo<idx>(cx, W, Wc), x1 = box_lo<idx>(cx + 1, W, Wc);
+        int y0 = box_lo<idx>(cy, H, Hc), y1 = box_lo<idx>(cy + 1, H, Hc);
+        int z0 = box_lo<idx>(cz, D, Dc), z1 = box_lo<idx>(cz + 1, D, Dc);
         if (x1 <= x0) { x0 = (int)(((2LL * cx + 1) * W) / (2LL * Wc)); x1 = x0 + 1; }
         if (y1 <= y0) { y0 = (int)(((2LL * cy + 1) * H) / (2LL * Hc)); y1 = y0 + 1; }
         if (z1 <= z0) { z0 = (int)(((2LL * cz + 1) * D) / (2LL * Dc)); z1 = z0 + 1; }
@@ -543,28 +596,33 @@ __global__ void k_target(const float *__restrict__ T, int D, int H, int W, float
 // scale * (T - T_lin)): trilinear interpolation between coarse voxel centres
 // (periodic in y and z, clamped in x), then T = T_lin(x) + pred / scale.
 // bad[block] counts values that are not finite or outside [-margin, 1 + margin].
+// idx: unsigned where the voxels fit 31 bits
+template <typename idx>
 __global__ void k_to_temperature(const float *__restrict__ pred, int cpred, int Dc, int Hc, int Wc, int D, int H, int W,
                                  float scale, float margin, float *__restrict__ T, int *__restrict__ bad) {
-    const long long total = (long long)D * H * W;
+    const idx total = (idx)D * H * W;
     const float rx = (float)Wc / (float)W, ry = (float)Hc / (float)H, rz = (float)Dc / (float)D;
     int nbad = 0;
-    for (long long v = blockIdx.x * (long long)blockDim.x + threadIdx.x; v < total; v += (long long)gridDim.x * blockDim.x) {
-        const int x = (int)(v % W);
-        const long long r = v / W;
-        const int y = (int)(r % H), z = (int)(r / H);
+    for (idx v = (idx)blockIdx.x * blockDim.x + threadIdx.x; v < total; v += (idx)gridDim.x * blockDim.x) {
+        const idx r = v / W;
+        const int x = (int)(v - r * W), z = (int)(r / H), y = (int)(r - (idx)z * H);
         // fine voxel centre in coarse-voxel-centre coordinates
         const float cx = ((float)x + 0.5f) * rx - 0.5f, cy = ((float)y + 0.5f) * ry - 0.5f,
                     cz = ((float)z + 0.5f) * rz - 0.5f;
         const float fx = floorf(cx), fy = floorf(cy), fz = floorf(cz);
         const float tx = cx - fx, ty = cy - fy, tz = cz - fz;
         float acc = 0.0f;
+#pragma unroll
         for (int dz = 0; dz < 2; dz++)
+#pragma unroll
             for (int dy = 0; dy < 2; dy++)
+#pragma unroll
                 for (int dx = 0; dx < 2; dx++) {
                     int ix = (int)fx + dx, iy = (int)fy + dy, iz = (int)fz + dz;
                     ix = min(max(ix, 0), Wc - 1);
-                    iy = ((iy % Hc) + Hc) % Hc;
-                    iz = ((iz % Dc) + Dc) % Dc;
+                    // from -1 to the extent: one wrap
+                    iy = iy < 0 ? iy + Hc : (iy >= Hc ? iy - Hc : iy);
+                    iz = iz < 0 ? iz + Dc : (iz >= Dc ? iz - Dc : iz);
                     const float wgt = (dx ? tx : 1.0f - tx) * (dy ? ty : 1.0f - ty) * (dz ? tz : 1.0f - tz);
                     acc += wgt * pred[(((long long)iz * Hc + iy) * Wc + ix) * cpred];
                 }
@@ -719,20 +777,40 @@ hipError_t nn_add(const void *a, const void *b, void *out, long long n, hipStrea
     return hipGetLastError();
 }
 
+// the kernels that take 8 channels per thread: whole groups, aligned, 32-bit indices
+static inline bool groups8(const void *in, const void *out, long long fine, int c) {
+    return c % 8 == 0 && aligned16(in) && aligned16(out) && fine / 8 < (1LL << 31);
+}
+
 hipError_t nn_pool2(int fwd, const void *in, int n, int D, int H, int W, int c, void *out, hipStream_t s) {
     const long long big = (long long)n * D * H * W * c;
-    if (fwd) hipLaunchKernelGGL(k_pool2_fwd, dim3(g1(big / 8)), dim3(256), 0, s, (const bf16 *)in, n, D, H, W, c, (bf16 *)out);
-    else hipLaunchKernelGGL(k_pool2_bwd, dim3(g1(big)), dim3(256), 0, s, (const bf16 *)in, n, D, H, W, c, (bf16 *)out);
+    if (groups8(in, out, big, c)) {
+        if (fwd)
+            hipLaunchKernelGGL(k_sum2_8, dim3(g1(big / 64)), dim3(256), 0, s, (const bf16x8 *)in, n, D / 2, H / 2, W / 2,
+                               c / 8, 0.125f, (bf16x8 *)out);
+        else
+            hipLaunchKernelGGL(k_pool2_bwd8, dim3(g1(big / 8)), dim3(256), 0, s, (const bf16x8 *)in, n, D, H, W, c / 8,
+                               (bf16x8 *)out);
+    } else if (fwd)
+        hipLaunchKernelGGL(k_pool2_fwd, dim3(g1(big / 8)), dim3(256), 0, s, (const bf16 *)in, n, D, H, W, c, (bf16 *)out);
+    else
+        hipLaunchKernelGGL(k_pool2_bwd, dim3(g1(big)), dim3(256), 0, s, (const bf16 *)in, n, D, H, W, c, (bf16 *)out);
     return hipGetLastError();
 }
 
 hipError_t nn_up2(int fwd, const void *in, int n, int D, int H, int W, int c, void *out, hipStream_t s) {
     const long long small = (long long)n * D * H * W * c;
-    if (fwd && c % 8 == 0 && aligned16(in) && aligned16(out))
-        hipLaunchKernelGGL(k_up2_fwd8, dim3(g1(small)), dim3(256), 0, s, (const bf16x8 *)in, n, D, H, W, c / 8,
-                           (bf16x8 *)out);
-    else if (fwd) hipLaunchKernelGGL(k_up2_fwd, dim3(g1(small * 8)), dim3(256), 0, s, (const bf16 *)in, n, D, H, W, c, (bf16 *)out);
-    else hipLaunchKernelGGL(k_up2_bwd, dim3(g1(small)), dim3(256), 0, s, (const bf16 *)in, n, D, H, W, c, (bf16 *)out);
+    if (groups8(in, out, small * 8, c)) {
+        if (fwd)
+            hipLaunchKernelGGL(k_up2_fwd8, dim3(g1(small)), dim3(256), 0, s, (const bf16x8 *)in, n, D, H, W, c / 8,
+                               (bf16x8 *)out);
+        else
+            hipLaunchKernelGGL(k_sum2_8, dim3(g1(small / 8)), dim3(256), 0, s, (const bf16x8 *)in, n, D, H, W, c / 8, 1.0f,
+                               (bf16x8 *)out);
+    } else if (fwd)
+        hipLaunchKernelGGL(k_up2_fwd, dim3(g1(small * 8)), dim3(256), 0, s, (const bf16 *)in, n, D, H, W, c, (bf16 *)out);
+    else
+        hipLaunchKernelGGL(k_up2_bwd, dim3(g1(small)), dim3(256), 0, s, (const bf16 *)in, n, D, H, W, c, (bf16 *)out);
     return hipGetLastError();
 }
 
@@ -769,8 +847,13 @@ hipError_t nn_features(const uint8_t *phase, int D, int H, int W, const float *f
 
 hipError_t nn_features_resampled(const uint8_t *phase, int D, int H, int W, const float *feat, int Dc, int Hc, int Wc,
                                  void *out, hipStream_t s) {
-    hipLaunchKernelGGL(k_features_resampled, dim3(g1((long long)Dc * Hc * Wc)), dim3(256), 0, s, phase, D, H, W, feat,
-                       Dc, Hc, Wc, (bf16 *)out);
+    const long long ext = std::max({D, H, W}), most = std::max({Dc, Hc, Wc});
+    if (2 * (most + 1) * ext < (1LL << 31) && (long long)Dc * Hc * Wc < (1LL << 31))
+        hipLaunchKernelGGL(k_features_resampled<unsigned>, dim3(g1((long long)Dc * Hc * Wc)), dim3(256), 0, s, phase, D, H,
+                           W, feat, Dc, Hc, Wc, (bf16 *)out);
+    else
+        hipLaunchKernelGGL(k_features_resampled<long long>, dim3(g1((long long)Dc * Hc * Wc)), dim3(256), 0, s, phase, D, H,
+                           W, feat, Dc, Hc, Wc, (bf16 *)out);
     return hipGetLastError();
 }
 
@@ -784,8 +867,12 @@ int nn_temp_blocks(long long n) { return g1(n) > 2048 ? 2048 : g1(n); }
 hipError_t nn_to_temperature(const float *pred, int cpred, int Dc, int Hc, int Wc, int D, int H, int W, float scale,
                              float margin, float *T, int *bad, hipStream_t s) {
     const long long n = (long long)D * H * W;
-    hipLaunchKernelGGL(k_to_temperature, dim3(nn_temp_blocks(n)), dim3(256), 0, s, pred, cpred, Dc, Hc, Wc, D, H, W,
-                       scale, margin, T, bad);
+    if (n < (1LL << 31))
+        hipLaunchKernelGGL(k_to_temperature<unsigned>, dim3(nn_temp_blocks(n)), dim3(256), 0, s, pred, cpred, Dc, Hc, Wc, D,
+                           H, W, scale, margin, T, bad);
+    else
+        hipLaunchKernelGGL(k_to_temperature<long long>, dim3(nn_temp_blocks(n)), dim3(256), 0, s, pred, cpred, Dc, Hc, Wc,
+                           D, H, W, scale, margin, T, bad);
     return hipGetLastError();
 }
 

@@ -9,10 +9,25 @@ namespace mrt {
 
 constexpr int TILE_X = 8;
 
-template <int TY, int TZ>
+// PITCH_: positions between neighbouring lines in LDS (at least 10).  A 16-byte
+// read of the matrix operand is free of bank conflicts when its 16 voxels lie
+// at 16 different positions modulo 16; a group is two lines of 8, so lines that
+// are 8 modulo 16 apart: y and y + 4 at pitch 10.
+template <int TY, int TZ, int PITCH_ = TILE_X + 2>
 struct Tile {
-    static constexpr int HX = TILE_X + 2, HY = TY + 2, HZ = TZ + 2;
-    static constexpr int HALO = HX * HY * HZ;  // voxels staged
+    static constexpr int HX = TILE_X + 2, HY = TY + 2, HZ = TZ + 2, PITCH = PITCH_;
+    static constexpr int HALO = HX * HY * HZ;      // voxels staged
+    static constexpr int SPAN = PITCH * HY * HZ;   // positions in LDS
+    static constexpr int PAIR = TY == 8 ? 4 : 1;   // lines of a group: y, y + PAIR
+
+    // position of staged voxel h
+    static __host__ __device__ constexpr int place(int h) { return h / HX * PITCH + h % HX; }
+    // offset of a tap in positions
+    static __host__ __device__ constexpr int tap(int t) { return ((t / 9) * HY + (t / 3) % 3) * PITCH + t % 3; }
+    // line (y + TY z) of half 0 or 1 of voxel group i
+    static __host__ __device__ constexpr int line(int i, int half) {
+        return i / PAIR * 2 * PAIR + i % PAIR + half * PAIR;
+    }
 
     // tile t of the launch: sample and first voxel
     int nb, x0, y0, z0;
@@ -51,12 +66,6 @@ struct Tile {
 
 inline long long tile_count(const ConvGeom &g, int ty, int tz) {
     return (long long)g.n * ((g.D + tz - 1) / tz) * ((g.H + ty - 1) / ty) * ((g.W + TILE_X - 1) / TILE_X);
-}
-
-// a tap's offset in halo positions
-template <int TY, int TZ>
-__host__ __device__ constexpr int tap_shift(int tap) {
-    return (tap / 9) * Tile<TY, TZ>::HX * Tile<TY, TZ>::HY + (tap / 3) % 3 * Tile<TY, TZ>::HX + tap % 3;
 }
 
 }  // namespace mrt

@@ -22,8 +22,10 @@
 
 namespace mrt {
 
-constexpr int WG_TY = 8, WG_TZ = 4;
-typedef Tile<WG_TY, WG_TZ> WTile;
+// pitch 12: the lines that two quarters of a wave read are 128 bytes apart
+// modulo the 256 of the banks
+constexpr int WG_TY = 8, WG_TZ = 4, WG_PITCH = 12;
+typedef Tile<WG_TY, WG_TZ, WG_PITCH> WTile;
 constexpr int WG_VOX = TILE_X * WG_TY * WG_TZ;
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -43,7 +45,7 @@ __device__ __forceinline__ bf16x8 tr_read(const char *p, int step) {
 }
 
 template <int CIN, int CO>
-__global__ void __launch_bounds__(256) k_wgrad_tile(const bf16 *__restrict__ x, const bf16 *__restrict__ dy, ConvGeom g,
+__global__ void __launch_bounds__(256, 2) k_wgrad_tile(const bf16 *__restrict__ x, const bf16 *__restrict__ dy, ConvGeom g,
                                                     int ntiles, float *__restrict__ partials) {
     constexpr int CB = CIN < 32 ? CIN : 32;      // input channels of the block
     constexpr int XP = CB < 16 ? 1 : CB / 16;    // planes of x: 16 channels (8: one plane of 8)
@@ -52,7 +54,7 @@ __global__ void __launch_bounds__(256) k_wgrad_tile(const bf16 *__restrict__ x, 
     constexpr int NT = CIN <= 16 ? (27 * CIN + 31) / 32 * 2 : 27 * XP;  // 16-column tiles (with the padding columns)
     constexpr int PW = (NT + 3) / 4;             // of one wave
     constexpr int XLINE = XC * 2;                // bytes of a position of x
-    constexpr int XPLANE = WTile::HALO * XLINE, DPLANE = WG_VOX * 32;
+    constexpr int XPLANE = WTile::SPAN * XLINE, DPLANE = WG_VOX * 32;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     char *xs = reinterpret_cast<char *>(smem_raw);
     char *ds = xs + XP * XPLANE;
@@ -86,7 +88,7 @@ __global__ void __launch_bounds__(256) k_wgrad_tile(const bf16 *__restrict__ x, 
         else if constexpr (CIN == 16) tap = n;
         else tap = n / XP, plane = n % XP;
         tzero[t] = tap >= 27;
-        toff[t] = tzero[t] ? 0 : tap_shift<WG_TY, WG_TZ>(tap) * XLINE + plane * XPLANE;
+        toff[t] = tzero[t] ? 0 : WTile::tap(tap) * XLINE + plane * XPLANE;
     }
     const int col = CIN == 8 ? (j & 1) * 8 : (j & 3) * 8;  // bytes
     const int row = j >> 2;
@@ -113,7 +115,7 @@ __global__ void __launch_bounds__(256) k_wgrad_tile(const bf16 *__restrict__ x, 
         for (int u = 0; u < XPER; u++) {
             const int i = u * 256 + threadIdx.x, c = i % XG;
             if (i < XITEMS)
-                *reinterpret_cast<bf16x8 *>(xs + (CB < 16 ? 0 : c / 2 * XPLANE) + i / XG * XLINE + (CB < 16 ? 0 : c % 2 * 16)) = xv[u];
+                *reinterpret_cast<bf16x8 *>(xs + (CB < 16 ? 0 : c / 2 * XPLANE) + WTile::place(i / XG) * XLINE + (CB < 16 ? 0 : c % 2 * 16)) = xv[u];
         }
 #pragma unroll
         for (int u = 0; u < DPER; u++) {
@@ -143,7 +145,7 @@ __global__ void __launch_bounds__(256) k_wgrad_tile(const bf16 *__restrict__ x, 
                     keep[e] = (line && tile.x0 + 2 * e < g.W ? 0xffffu : 0u) |
                               (line && tile.x0 + 2 * e + 1 < g.W ? 0xffff0000u : 0u);
             }
-            const char *xl = xs + ((z * WTile::HY + y) * WTile::HX + row) * XLINE + col;
+            const char *xl = xs + ((z * WTile::HY + y) * WG_PITCH + row) * XLINE + col;
 #pragma unroll
             for (int t = 0; t < PW; t++) {
                 if (t * 4 + 3 >= NT && t * 4 + wave >= NT) continue;
@@ -219,7 +221,7 @@ bool nn_wgrad_tile_takes(const ConvGeom &g) {
 template <int CIN, int CO>
 static void launch_wgrad(const bf16 *x, const bf16 *dy, const ConvGeom &g, float *partials, hipStream_t s) {
     constexpr int CB = CIN < 32 ? CIN : 32;
-    constexpr size_t lds = (size_t)WTile::HALO * CB * 2 + (size_t)WG_VOX * CO * 2 + 256;
+    constexpr size_t lds = (size_t)WTile::SPAN * CB * 2 + (size_t)WG_VOX * CO * 2 + 256;
     const dim3 grid((unsigned)wgrad_groups(g), (unsigned)nn_wgrad_tile_splits(g));
     hipLaunchKernelGGL((k_wgrad_tile<CIN, CO>), grid, dim3(256), lds, s, x, dy, g, (int)tile_count(g, WG_TY, WG_TZ), partials);
 }
