@@ -144,7 +144,7 @@ size_t mrt::partial_capacity(int nx, int ny) { return (size_t)((nx + 15) / 16) *
 
 // the small arrays first, so that their offsets do not depend on the state
 // storage; then the two state buffers of `values` reals per node
-static bool layout(int nx, int ny, int nz, int nphase, mrtlbm_precision p, int values, size_t off[5],
+static bool layout(int nx, int ny, int nz, int nphase, mrtlbm_precision p, int values, size_t off[4],
                    size_t *total) {
     if (nx < 1 || ny < 1 || nz < 1 || nphase < 1 || nphase > 256) return false;
     if (nz > 65535 || (long long)ny > 65535LL * 16) return false;
@@ -152,8 +152,7 @@ static bool layout(int nx, int ny, int nz, int nphase, mrtlbm_precision p, int v
     const size_t N = (size_t)nx * ny * nz;
     size_t o = 0;
     off[2] = o; o = align256(o + partial_capacity(nx, ny) * NRED * 8); // partials
-    off[3] = o; o = align256(o + 16 * 8);                              // final reduction
-    off[4] = o; o = align256(o + (size_t)nphase * TABW * rs);          // phase tables
+    off[3] = o; o = align256(o + (size_t)nphase * TABW * rs);          // phase tables
     off[0] = o; o = align256(o + values * N * rs);                     // buffer A
     off[1] = o; o = align256(o + values * N * rs);                     // buffer B
     *total = o;
@@ -164,7 +163,7 @@ static int state_values_of(int storage) { return storage ? 4 : Q; }
 
 extern "C" size_t mrtlbm_workspace_bytes_storage(int nx, int ny, int nz, int nphase, mrtlbm_precision p,
                                                  int storage) {
-    size_t off[5], total;
+    size_t off[4], total;
     if ((p != MRTLBM_F32 && p != MRTLBM_F64) || (storage != 0 && storage != 1)) return 0;
     return layout(nx, ny, nz, nphase, p, state_values_of(storage), off, &total) ? total : 0;
 }
@@ -290,7 +289,7 @@ extern "C" mrtlbm_status mrtlbm_create(int nx, int ny, int nz, const unsigned ch
     if (!out) return fail(MRTLBM_E_ARG, "out is NULL");
     *out = nullptr;
     if (p != MRTLBM_F32 && p != MRTLBM_F64) return fail(MRTLBM_E_ARG, "bad precision %d", (int)p);
-    size_t off[5], total, off7[5], total7;
+    size_t off[4], total, off7[4], total7;
     if (!layout(nx, ny, nz, nphase, p, 4, off, &total) || !layout(nx, ny, nz, nphase, p, Q, off7, &total7))
         return fail(MRTLBM_E_ARG, "bad sizes nx=%d ny=%d nz=%d nphase=%d", nx, ny, nz, nphase);
     if (!phase_dev || !k_host) return fail(MRTLBM_E_ARG, "phase_dev or k_host is NULL");
@@ -324,8 +323,7 @@ extern "C" mrtlbm_status mrtlbm_create(int nx, int ny, int nz, const unsigned ch
     m->bufA = w + off[0];
     m->bufB = w + off[1];
     m->partials = (double *)(w + off[2]);
-    m->final8 = (double *)(w + off[3]);
-    m->tab = w + off[4];
+    m->tab = w + off[3];
     m->storage = storage;
     m->pcap = partial_capacity(nx, ny);
     m->stream = (hipStream_t)hip_stream;
@@ -500,16 +498,16 @@ static hipError_t check_step(mrtlbm_medium *m, int mode, hipStream_t s, int *cur
     if ((size_t)check_blocks<real>(c, m->launch) > m->pcap) return hipErrorInvalidValue;
     int nb = 0;
     hipError_t e = launch_check<real>(c, m->launch, mode, m->partials, &nb, (real *)qout, qscale, s);
-    if (e != hipSuccess) return e;
-    e = launch_reduce(m->partials, nb, m->final8, s);
+    if (e != hipSuccess || mode == 3) return e;  // a flux field leaves nothing to sum
+    e = launch_reduce(m->partials, nb, m->pinned, s);
     if (e != hipSuccess) return e;
     if (mode == 1) *cur ^= 1;
     return hipSuccess;
 }
 
 // Graph of `K` steps starting from buffer parity `cur`: K-1 plain steps, then
-// (if with_check) one step that also evaluates the observables, the final
-// reduction and a copy of the 8 doubles to pinned host memory.
+// (if with_check) one step that also evaluates the observables and the final
+// reduction, which leaves its sums in pinned host memory.
 template <typename real>
 static mrtlbm_status get_graph(mrtlbm_medium *m, int K, bool with_check, hipGraphExec_t *exec) {
     for (auto &g : m->graphs)
@@ -522,8 +520,6 @@ static mrtlbm_status get_graph(mrtlbm_medium *m, int K, bool with_check, hipGrap
     int cur = m->cur;
     hipError_t e = plain_steps<real>(m, with_check ? K - 1 : K, true, m->cap_stream, &cur);
     if (e == hipSuccess && with_check) e = check_step<real>(m, 1, m->cap_stream, &cur, nullptr, 0.0);
-    if (e == hipSuccess && with_check)
-        e = hipMemcpyAsync(m->pinned, m->final8, NRED * sizeof(double), hipMemcpyDeviceToHost, m->cap_stream);
     hipGraph_t graph = nullptr;
     hipError_t e2 = hipStreamEndCapture(m->cap_stream, &graph);
     if (e != hipSuccess) {
@@ -619,7 +615,6 @@ extern "C" mrtlbm_status mrtlbm_keff(mrtlbm_medium *m, mrtlbm_result *out) {
     hipError_t e = (m->prec == MRTLBM_F64) ? check_step<double>(m, 2, m->stream, &cur, nullptr, 0.0)
                                            : check_step<float>(m, 2, m->stream, &cur, nullptr, 0.0);
     if (e != hipSuccess) return hip_fail(e, "observables");
-    HIPCHK(hipMemcpyAsync(m->pinned, m->final8, NRED * sizeof(double), hipMemcpyDeviceToHost, m->stream));
     HIPCHK(hipStreamSynchronize(m->stream));
     fill_result(m, m->pinned, out);
     return out->nonfinite ? fail(MRTLBM_E_NONFINITE, "%d non-finite nodes", out->nonfinite) : MRTLBM_OK;
@@ -718,7 +713,6 @@ static mrtlbm_status do_solve(mrtlbm_medium *m, double tol, mrtlbm_tol_kind kind
             int cur = m->cur;
             HIPCHK(plain_steps<real>(m, left - 1, false, m->stream, &cur));
             HIPCHK(check_step<real>(m, 1, m->stream, &cur, nullptr, 0.0));
-            HIPCHK(hipMemcpyAsync(m->pinned, m->final8, NRED * sizeof(double), hipMemcpyDeviceToHost, m->stream));
             m->cur = cur;
             m->steps += left;
         }
@@ -761,7 +755,7 @@ extern "C" mrtlbm_status mrtlbm_set_storage(mrtlbm_medium *m, int storage) {
     if (storage != 0 && storage != 1) return fail(MRTLBM_E_ARG, "storage must be 0 or 1");
     if (storage == 1 && (m->tau_rest[0] != 1.0 || m->tau_rest[1] != 1.0 || m->tau_rest[2] != 1.0))
         return fail(MRTLBM_E_ARG, "moment storage holds only tau_4 = tau_5 = tau_6 = 1");
-    size_t off[5], total;
+    size_t off[4], total;
     layout(m->nx, m->ny, m->nz, m->nphase, m->prec, state_values_of(storage), off, &total);
     if (total > m->ws_bytes)
         return fail(MRTLBM_E_WORKSPACE, "workspace of %zu bytes, storage %d needs %zu", m->ws_bytes, storage, total);

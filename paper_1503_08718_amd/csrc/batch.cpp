@@ -18,7 +18,7 @@ namespace {
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
 struct BatchLayout {
-    size_t cells, tiles, partials, start, finals, total;
+    size_t cells, tiles, partials, start, total;
     long long max_tiles;
 };
 
@@ -38,7 +38,6 @@ bool batch_layout(mrtlbm_medium *const *cells, int n, BatchLayout *L) {
     L->tiles = o; o = align256(o + (size_t)mt * sizeof(int4));
     L->partials = o; o = align256(o + (size_t)mt * NRED * sizeof(double));
     L->start = o; o = align256(o + (size_t)(n + 1) * sizeof(int));
-    L->finals = o; o = align256(o + (size_t)n * NRED * sizeof(double));
     L->total = o;
     L->max_tiles = mt;
     return true;
@@ -164,7 +163,6 @@ mrtlbm_status build_graph(BatchRun &B, int K) {
     const int4 *tiles = (const int4 *)(B.ws + B.lay.tiles);
     double *partials = (double *)(B.ws + B.lay.partials);
     const int *start = (const int *)(B.ws + B.lay.start);
-    double *finals = (double *)(B.ws + B.lay.finals);
     hipError_t e = hipStreamBeginCapture(B.cap, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
     // an even number of pairs: the buffers have changed places an even number
@@ -175,9 +173,7 @@ mrtlbm_status build_graph(BatchRun &B, int K) {
     for (int i = 0; i < K - 2 * pairs && e == hipSuccess; i++)
         e = launch_batch<real>(cells, tiles, B.ntiles, B.vec, B.threads, B.max_nphase, i & 1, i == K - 2 * pairs - 1,
                                B.nt, B.chunk, B.storage, partials, B.cap);
-    if (e == hipSuccess) e = launch_batch_reduce(partials, start, (int)B.active.size(), finals, B.cap);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(B.pinned, finals, B.active.size() * NRED * sizeof(double), hipMemcpyDeviceToHost, B.cap);
+    if (e == hipSuccess) e = launch_batch_reduce(partials, start, (int)B.active.size(), B.pinned, B.cap);
     hipGraph_t g = nullptr;
     hipError_t e2 = hipStreamEndCapture(B.cap, &g);
     if (e != hipSuccess) {

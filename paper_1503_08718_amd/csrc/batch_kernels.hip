@@ -72,25 +72,7 @@ __global__ void __launch_bounds__(256) k_batch(const Cell<real> *__restrict__ ce
 // one block per cell: fixed-order sum of that cell's tile partials
 __global__ void __launch_bounds__(256) k_batch_reduce(const double *__restrict__ partials, const int *__restrict__ start,
                                                       double *__restrict__ finals) {
-    __shared__ double red[256][NRED];
-    const int cell = blockIdx.x, t = threadIdx.x;
-    const int b = start[cell], e = start[cell + 1];
-    double v[NRED];
-    for (int k = 0; k < NRED; k++) v[k] = 0.0;
-    for (int i = b + t; i < e; i += 256)
-        for (int k = 0; k < NRED; k++) {
-            const double p = partials[(long long)i * NRED + k];
-            v[k] = (k == R_RESID) ? fmax(v[k], p) : v[k] + p;
-        }
-    for (int k = 0; k < NRED; k++) red[t][k] = v[k];
-    __syncthreads();
-    for (int s = 128; s >= 1; s >>= 1) {
-        if (t < s)
-            for (int k = 0; k < NRED; k++)
-                red[t][k] = (k == R_RESID) ? fmax(red[t][k], red[t + s][k]) : red[t][k] + red[t + s][k];
-        __syncthreads();
-    }
-    if (t < NRED) finals[(long long)cell * NRED + t] = red[0][t];
+    reduce_partials(partials, start[blockIdx.x], start[blockIdx.x + 1], finals + (long long)blockIdx.x * NRED);
 }
 
 template <typename real, int VEC, int ST>

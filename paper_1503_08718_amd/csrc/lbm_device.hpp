@@ -99,8 +99,10 @@ struct Pulled {
     bool hot, cold;            // this thread holds nodes on the hot / cold face
 };
 
+__host__ __device__ constexpr bool observes(int mode) { return mode == 1 || mode == 2; }
+
 // Distribution storage: state [7][N].
-// MODE 0: step; 1: step + observables; 2: observables only; 3: as 2 + flux field.
+// MODE 0: step; 1: step + observables; 2: observables only; 3: flux field only.
 // NT bit 0: non-temporal state loads; bit 1: non-temporal state stores.
 template <typename real, int VEC, int MODE, int NT>
 __device__ __forceinline__ void pull_dist(const Cell<real> &c, int xv, int y, int z, const XLink &xl,
@@ -129,7 +131,7 @@ __device__ __forceinline__ void pull_dist(const Cell<real> &c, int xv, int y, in
     Vec<real, VEC> b5 = vload<real, VEC, NL>(s + pzm * N + ((long long)zm * ny + y) * nx + x0);
     Vec<real, VEC> b6 = vload<real, VEC, NL>(s + pzp * N + ((long long)zp * ny + y) * nx + x0);
     load_phase<VEC>(c.phase + base, P.ph);
-    if constexpr (MODE != 0) {  // own post-collision populations: T(t) for the residual
+    if constexpr (observes(MODE)) {  // own post-collision populations: T(t) for the residual
         Vec<real, VEC> o3 = vload<real, VEC>(s + 3 * N + base);
         Vec<real, VEC> o4 = vload<real, VEC>(s + 4 * N + base);
         Vec<real, VEC> o5 = vload<real, VEC>(s + 5 * N + base);
@@ -173,7 +175,7 @@ __device__ __forceinline__ void pull_dist(const Cell<real> &c, int xv, int y, in
         P.r[4][v] = fma(sz5, b5.v[v], pz5);
         P.r[5][v] = fma(sz6, b6.v[v], pz6);
     }
-    if constexpr (MODE != 0) {
+    if constexpr (observes(MODE)) {
         P.out_hot = P.out_cold = 0.0;
         const int g = c.gaxis;
         if (g == 0) {
@@ -257,7 +259,7 @@ __device__ __forceinline__ void pull_mom(const Cell<real> &c, int xv, int y, int
         right = xl.haveR ? gotR : gminus(sT[base + VEC], sX[base + VEC]);
     }
     Vec<real, VEC> Yc, Zc;
-    if constexpr (MODE != 0) {
+    if constexpr (observes(MODE)) {
         Yc = vload<real, VEC>(sY + base);
         Zc = vload<real, VEC>(sZ + base);
     }
@@ -270,13 +272,13 @@ __device__ __forceinline__ void pull_mom(const Cell<real> &c, int xv, int y, int
         P.r[3][v] = wyp ? fma(c.sgn[1], gplus(Typ.v[v], Yyp.v[v]), c.phi[1][1]) : gminus(Typ.v[v], Yyp.v[v]);
         P.r[4][v] = wzm ? fma(c.sgn[2], gminus(Tzm.v[v], Zzm.v[v]), c.phi[2][0]) : gplus(Tzm.v[v], Zzm.v[v]);
         P.r[5][v] = wzp ? fma(c.sgn[2], gplus(Tzp.v[v], Zzp.v[v]), c.phi[2][1]) : gminus(Tzp.v[v], Zzp.v[v]);
-        if constexpr (MODE != 0) {
+        if constexpr (observes(MODE)) {
             const real t = Tc.v[v];
             P.told[v] = t * real(0.25) + gplus(t, Xc.v[v]) + gminus(t, Xc.v[v]) + gplus(t, Yc.v[v]) +
                         gminus(t, Yc.v[v]) + gplus(t, Zc.v[v]) + gminus(t, Zc.v[v]);
         }
     }
-    if constexpr (MODE != 0) {
+    if constexpr (observes(MODE)) {
         P.out_hot = P.out_cold = 0.0;
         const int g = c.gaxis;
         if (g == 0) {
@@ -368,6 +370,20 @@ __device__ __forceinline__ void relax_general(const real *srel, real f0, real f1
     o[6] = az - hjz;
 }
 
+// The flux of a thread's nodes; the caller's array may lie anywhere.
+template <typename real, int VEC>
+__device__ __forceinline__ void store_flux(real *__restrict__ q, long long N, long long base, const Vec<real, VEC> *F) {
+    if ((reinterpret_cast<uintptr_t>(q) & (VEC * sizeof(real) - 1)) == 0) {
+#pragma unroll
+        for (int a = 0; a < 3; a++) vstore<real, VEC, false>(q + a * N + base, F[a]);
+    } else {
+#pragma unroll
+        for (int a = 0; a < 3; a++)
+#pragma unroll
+            for (int v = 0; v < VEC; v++) q[a * N + base + v] = F[a].v[v];
+    }
+}
+
 // Collision (shared by all storages), FP64 observables, and the stores.
 // STORAGE 0: 7 populations; 1: 4 moments; 2: 7 populations, general tau_4..6.
 template <typename real, int VEC, int MODE, int NT, int STORAGE>
@@ -377,6 +393,7 @@ __device__ __forceinline__ void collide_store(const Cell<real> &c, const real *_
     const long long N = c.N;
     const long long base = ((long long)z * c.ny + y) * c.nx + xv * VEC;
     const real hx = c.h[0], hy = c.h[1], hz = c.h[2];
+    Vec<real, VEC> F_[MODE == 3 ? 3 : 1];  // flux
     Vec<real, VEC> T_, X_, Y_, Z_;
     Vec<real, VEC> G_[STORAGE == 2 ? Q : 1];  // general relaxation: the seven outputs
 #pragma unroll
@@ -425,11 +442,15 @@ __device__ __forceinline__ void collide_store(const Cell<real> &c, const real *_
             for (int i = 0; i < Q; i++) G_[i].v[v] = o[i];
         }
         if constexpr (MODE != 0) {
-            if (active) {
+            const double qx = 0.5 * (double)jx + (double)hjx;
+            const double qy = 0.5 * (double)jy + (double)hjy;
+            const double qz = 0.5 * (double)jz + (double)hjz;
+            if constexpr (MODE == 3) {
+                F_[0].v[v] = (real)(qx * (double)qscale);
+                F_[1].v[v] = (real)(qy * (double)qscale);
+                F_[2].v[v] = (real)(qz * (double)qscale);
+            } else if (active) {
                 const double dT = fabs((double)T - (double)P.told[v]);
-                const double qx = 0.5 * (double)jx + (double)hjx;
-                const double qy = 0.5 * (double)jy + (double)hjy;
-                const double qz = 0.5 * (double)jz + (double)hjz;
                 acc.v[R_QX] += qx;
                 acc.v[R_QY] += qy;
                 acc.v[R_QZ] += qz;
@@ -453,16 +474,10 @@ __device__ __forceinline__ void collide_store(const Cell<real> &c, const real *_
                 acc.v[R_LEAK] += dout - din;
                 if (!(dT <= 1e300)) acc.v[R_NONFINITE] += 1.0;
                 else acc.v[R_RESID] = fmax(acc.v[R_RESID], dT);
-                if constexpr (MODE == 3) {
-                    const long long i = base + v;
-                    qout[i] = (real)(qx * (double)qscale);
-                    qout[N + i] = (real)(qy * (double)qscale);
-                    qout[2 * N + i] = (real)(qz * (double)qscale);
-                }
             }
         }
     }
-    if constexpr (MODE != 0) {
+    if constexpr (observes(MODE)) {
         if (active) {
             // wall link fluxes through the isothermal faces:
             // hot:  eps (T_hot - T_lin(0)) - 2 g_out = h - 2 g_out
@@ -472,6 +487,9 @@ __device__ __forceinline__ void collide_store(const Cell<real> &c, const real *_
             if (P.hot) acc.v[R_PHI_HOT] += nodes * hg - 2.0 * P.out_hot;
             if (P.cold) acc.v[R_PHI_COLD] += 2.0 * P.out_cold + nodes * hg;
         }
+    }
+    if constexpr (MODE == 3) {
+        if (active) store_flux<real, VEC>(qout, N, base, F_);
     }
     if constexpr (MODE <= 1) {
         if (active) {
@@ -614,7 +632,7 @@ __device__ __forceinline__ void pull_mom_exact(const Cell<float> &c, int xv, int
         }
         P.told[v] = Tc.v[v];
     }
-    if constexpr (MODE != 0) {
+    if constexpr (observes(MODE)) {
         P.out_hot = P.out_cold = 0.0;
         const int g = c.gaxis;
         if (g == 0) {
@@ -641,6 +659,7 @@ __device__ __forceinline__ void collide_store_exact(const Cell<float> &c, const 
                                                     float *__restrict__ qout, float qscale) {
     const long long N = c.N;
     const long long base = ((long long)z * c.ny + y) * c.nx + xv * VEC;
+    Vec<float, VEC> F_[MODE == 3 ? 3 : 1];  // flux
     Vec<float, VEC> T_, X_, Y_, Z_;
 #pragma unroll
     for (int v = 0; v < VEC; v++) {
@@ -654,12 +673,16 @@ __device__ __forceinline__ void collide_store_exact(const Cell<float> &c, const 
         Y_.v[v] = fmaf(tb[5], jz, fmaf(tb[1], jy, tb[3] * jx));
         Z_.v[v] = fmaf(tb[2], jz, fmaf(tb[5], jy, tb[4] * jx));
         if constexpr (MODE != 0) {
-            if (active) {
-                const double jx64 = P.j64[0][v], jy64 = P.j64[1][v], jz64 = P.j64[2][v];
-                const double hx = fma((double)tb[4], jz64, fma((double)tb[3], jy64, (double)tb[0] * jx64));
-                const double hy = fma((double)tb[5], jz64, fma((double)tb[1], jy64, (double)tb[3] * jx64));
-                const double hz = fma((double)tb[2], jz64, fma((double)tb[5], jy64, (double)tb[4] * jx64));
-                const double qx = 0.5 * jx64 + hx, qy = 0.5 * jy64 + hy, qz = 0.5 * jz64 + hz;
+            const double jx64 = P.j64[0][v], jy64 = P.j64[1][v], jz64 = P.j64[2][v];
+            const double hx = fma((double)tb[4], jz64, fma((double)tb[3], jy64, (double)tb[0] * jx64));
+            const double hy = fma((double)tb[5], jz64, fma((double)tb[1], jy64, (double)tb[3] * jx64));
+            const double hz = fma((double)tb[2], jz64, fma((double)tb[5], jy64, (double)tb[4] * jx64));
+            const double qx = 0.5 * jx64 + hx, qy = 0.5 * jy64 + hy, qz = 0.5 * jz64 + hz;
+            if constexpr (MODE == 3) {
+                F_[0].v[v] = (float)(qx * (double)qscale);
+                F_[1].v[v] = (float)(qy * (double)qscale);
+                F_[2].v[v] = (float)(qz * (double)qscale);
+            } else if (active) {
                 acc.v[R_QX] += qx;
                 acc.v[R_QY] += qy;
                 acc.v[R_QZ] += qz;
@@ -670,22 +693,19 @@ __device__ __forceinline__ void collide_store_exact(const Cell<float> &c, const 
                 const double dT = fabs((double)T - (double)P.told[v]);
                 if (!(dT <= 1e300)) acc.v[R_NONFINITE] += 1.0;
                 else acc.v[R_RESID] = fmax(acc.v[R_RESID], dT);
-                if constexpr (MODE == 3) {
-                    const long long i = base + v;
-                    qout[i] = (float)(qx * (double)qscale);
-                    qout[N + i] = (float)(qy * (double)qscale);
-                    qout[2 * N + i] = (float)(qz * (double)qscale);
-                }
             }
         }
     }
-    if constexpr (MODE != 0) {
+    if constexpr (observes(MODE)) {
         if (active) {
             const double hg = (double)c.h[c.gaxis];
             const double nodes = (c.gaxis == 0) ? 1.0 : (double)VEC;
             if (P.hot) acc.v[R_PHI_HOT] += nodes * hg - 2.0 * P.out_hot;
             if (P.cold) acc.v[R_PHI_COLD] += 2.0 * P.out_cold + nodes * hg;
         }
+    }
+    if constexpr (MODE == 3) {
+        if (active) store_flux<float, VEC>(qout, N, base, F_);
     }
     if constexpr (MODE <= 1) {
         if (active) {
@@ -718,6 +738,7 @@ __device__ __forceinline__ void collide_store_pop32(const Cell<float> &c, const 
         srel[1] = c.srel[1];
         srel[2] = c.srel[2];
     }
+    Vec<float, VEC> F_[MODE == 3 ? 3 : 1];  // flux
     Vec<float, VEC> G[Q];
 #pragma unroll
     for (int v = 0; v < VEC; v++) {
@@ -747,12 +768,16 @@ __device__ __forceinline__ void collide_store_pop32(const Cell<float> &c, const 
             G[6].v[v] = dither_to_float(fma(T, 0.125, -hjz), key + 6);
         }
         if constexpr (MODE != 0) {
-            if (active) {
+            const double qx = 0.5 * jx + hjx, qy = 0.5 * jy + hjy, qz = 0.5 * jz + hjz;
+            if constexpr (MODE == 3) {
+                F_[0].v[v] = (float)(qx * (double)qscale);
+                F_[1].v[v] = (float)(qy * (double)qscale);
+                F_[2].v[v] = (float)(qz * (double)qscale);
+            } else if (active) {
                 // T(t+1) as the next step sums it; the rounding energy is its
                 // difference to the exact T
                 const double Tn = (double)G[0].v[v] + (double)G[1].v[v] + (double)G[2].v[v] + (double)G[3].v[v] +
                                   (double)G[4].v[v] + (double)G[5].v[v] + (double)G[6].v[v];
-                const double qx = 0.5 * jx + hjx, qy = 0.5 * jy + hjy, qz = 0.5 * jz + hjz;
                 acc.v[R_QX] += qx;
                 acc.v[R_QY] += qy;
                 acc.v[R_QZ] += qz;
@@ -761,22 +786,19 @@ __device__ __forceinline__ void collide_store_pop32(const Cell<float> &c, const 
                 const double dT = fabs(Tn - (double)P.told[v]);
                 if (!(dT <= 1e300)) acc.v[R_NONFINITE] += 1.0;
                 else acc.v[R_RESID] = fmax(acc.v[R_RESID], dT);
-                if constexpr (MODE == 3) {
-                    const long long i = base + v;
-                    qout[i] = (float)(qx * (double)qscale);
-                    qout[N + i] = (float)(qy * (double)qscale);
-                    qout[2 * N + i] = (float)(qz * (double)qscale);
-                }
             }
         }
     }
-    if constexpr (MODE != 0) {
+    if constexpr (observes(MODE)) {
         if (active) {
             const double hg = (double)c.h[c.gaxis];
             const double nodes = (c.gaxis == 0) ? 1.0 : (double)VEC;
             if (P.hot) acc.v[R_PHI_HOT] += nodes * hg - 2.0 * P.out_hot;
             if (P.cold) acc.v[R_PHI_COLD] += 2.0 * P.out_cold + nodes * hg;
         }
+    }
+    if constexpr (MODE == 3) {
+        if (active) store_flux<float, VEC>(qout, N, base, F_);
     }
     if constexpr (MODE <= 1) {
         if (active) {
@@ -853,29 +875,82 @@ __device__ __forceinline__ void table_commit(const Cell<real> &c, real *tab, con
     __syncthreads();
 }
 
-// deterministic block reduction of the 8 accumulators (sums, one max)
-__device__ __forceinline__ void block_reduce_store(Acc &acc, double *out) {
-    __shared__ double red[16][NRED];
+// One halving of the accumulators over the lanes `off` apart: of N values the
+// lanes with that bit clear keep the first KEEP, the others the rest, each
+// combined with its partner's.  max0: the first value kept is a maximum.
+template <int N, int KEEP>
+__device__ __forceinline__ void halve(double *v, int lane, int off, bool max0) {
+    const bool upper = (lane & off) != 0;
 #pragma unroll
-    for (int k = 0; k < NRED; k++) {
-        double v = acc.v[k];
-        for (int off = 32; off >= 1; off >>= 1) {
-            double o = __shfl_xor(v, off, 64);
-            v = (k == R_RESID) ? fmax(v, o) : v + o;
-        }
-        acc.v[k] = v;
-    }
-    const int tid = threadIdx.y * blockDim.x + threadIdx.x;
-    const int wave = tid >> 6, nw = (blockDim.x * blockDim.y + 63) >> 6;
-    if ((tid & 63) == 0)
-        for (int k = 0; k < NRED; k++) red[wave][k] = acc.v[k];
-    __syncthreads();
-    if (tid < NRED) {
-        double v = red[0][tid];
-        for (int w = 1; w < nw; w++) v = (tid == R_RESID) ? fmax(v, red[w][tid]) : v + red[w][tid];
-        out[tid] = v;
+    for (int i = 0; i < KEEP; i++) {
+        const double lo = v[i], hi = KEEP + i < N ? v[KEEP + i] : 0.0;
+        const double mine = upper ? hi : lo, theirs = __shfl_xor(upper ? lo : hi, off, 64);
+        v[i] = i == 0 && max0 ? fmax(mine, theirs) : mine + theirs;
     }
 }
 
+// Deterministic block reduction of the accumulators (sums, one max), whole
+// waves.  The first steps halve the values a lane carries instead of
+// exchanging all of them: 13 FP64 exchanges where ten butterflies take 60, with
+// the same sums in the same order (lanes 32, 16, ... 1 apart, then the waves).
+__device__ __forceinline__ void block_reduce_store(Acc &acc, double *out) {
+    static_assert(NRED == 10 && R_RESID == 5, "the halving below");
+    __shared__ double red[16][NRED];
+    const int tid = threadIdx.y * blockDim.x + threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6, nw = (blockDim.x * blockDim.y + 63) >> 6;
+    // R_RESID: first value of the upper half, then always of the lower part
+    const bool b5 = (lane & 32) != 0, b4 = (lane & 16) != 0, b3 = (lane & 8) != 0, b2 = (lane & 4) != 0;
+    bool resid = b5;
+    halve<10, 5>(acc.v, lane, 32, resid);
+    resid = resid && !b4;
+    halve<5, 3>(acc.v, lane, 16, resid);
+    resid = resid && !b3;
+    halve<3, 2>(acc.v, lane, 8, resid);
+    resid = resid && !b2;
+    halve<2, 1>(acc.v, lane, 4, resid);
+    double v = acc.v[0];
+#pragma unroll
+    for (int off = 2; off >= 1; off >>= 1) {
+        const double o = __shfl_xor(v, off, 64);
+        v = resid ? fmax(v, o) : v + o;
+    }
+    // the quantity this lane ended with; positions behind the last one are void
+    const int in3 = (b3 ? 2 : 0) + (b2 ? 1 : 0), in5 = (b4 ? 3 : 0) + in3;
+    if ((lane & 3) == 0 && in3 < 3 && in5 < 5) red[wave][(b5 ? 5 : 0) + in5] = v;
+    __syncthreads();
+    if (tid < NRED) {
+        double r = red[0][tid];
+        for (int w = 1; w < nw; w++) r = (tid == R_RESID) ? fmax(r, red[w][tid]) : r + red[w][tid];
+        out[tid] = r;
+    }
+}
+
+// Sum of the partials b .. e - 1 (one max) by one block of whole waves: each
+// thread takes every blockDim.x-th, several rows of ten in flight, then as above.
+__device__ __forceinline__ void reduce_partials(const double *__restrict__ partials, int b, int e, double *out) {
+    Acc acc;
+    acc.zero();
+    const int n = blockDim.x;
+    int i = b + threadIdx.x;
+    for (; i + n < e; i += 2 * n) {
+        double p[2][NRED];
+#pragma unroll
+        for (int u = 0; u < 2; u++)
+#pragma unroll
+            for (int k = 0; k < NRED; k++) p[u][k] = partials[(long long)(i + u * n) * NRED + k];
+#pragma unroll
+        for (int u = 0; u < 2; u++)
+#pragma unroll
+            for (int k = 0; k < NRED; k++) acc.v[k] = (k == R_RESID) ? fmax(acc.v[k], p[u][k]) : acc.v[k] + p[u][k];
+    }
+    if (i < e) {
+#pragma unroll
+        for (int k = 0; k < NRED; k++) {
+            const double p = partials[(long long)i * NRED + k];
+            acc.v[k] = (k == R_RESID) ? fmax(acc.v[k], p) : acc.v[k] + p;
+        }
+    }
+    block_reduce_store(acc, out);
+}
 
 }  // namespace mrt

@@ -47,14 +47,14 @@ template <typename real>
 hipError_t launch_step(const Cell<real> &c, const Launch &L, hipStream_t s);
 
 // mode 1: step + FP64 observables; mode 2: observables only (state unchanged);
-// mode 3: as 2 and also write the node flux field q_out ([3][N], scaled by qscale)
+// mode 3: only the node flux field q_out ([3][N], scaled by qscale); no partials
 template <typename real>
 hipError_t launch_check(const Cell<real> &c, const Launch &L, int mode, double *partials, int *nblocks_out,
                         real *q_out, double qscale, hipStream_t s);
 template <typename real>
 int check_blocks(const Cell<real> &c, const Launch &L);
 
-hipError_t launch_reduce(const double *partials, int nparts, double *final8, hipStream_t s);
+hipError_t launch_reduce(const double *partials, int nparts, double *sums, hipStream_t s);
 
 template <typename real>
 hipError_t launch_init(const Cell<real> &c, real *state, const real *t0, int flags, double t_hot, double dT,

@@ -104,12 +104,18 @@ __global__ void __launch_bounds__(256) k_step(Cell<real> c) {
 
 // Observables (and optionally the step): the grid covers x and y like the
 // step kernel; each block walks `zper` consecutive planes so that the number
-// of partials stays small and the summation order is fixed.
+// of partials stays small and the summation order is fixed.  FP64 arithmetic on
+// 100 to 160 VGPRs bounds it (three or four waves per SIMD; capped at 128 VGPRs
+// it spills, 18.9 -> 21 us at 128^3 FP32, and with a third of the blocks it
+// takes 26).  A flux field needs none of the sums: 22.9 -> 16.2 us without
+// them and with 16-byte stores.
 template <typename real, int VEC, int MODE, int ST>
 __global__ void __launch_bounds__(256) k_check(Cell<real> c, int zper, double *partials, real *qout, real qscale) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     real *tab = reinterpret_cast<real *>(smem_raw);
-    load_table(c, tab);
+    // the table is staged behind the first plane's loads
+    const TablePrefetch<real> tp = table_prefetch(c);
+    bool staged = false;
     const int tx = threadIdx.x, bx = blockDim.x;
     int xv = blockIdx.x * bx + tx;
     int y = blockIdx.y * blockDim.y + threadIdx.y;
@@ -120,30 +126,20 @@ __global__ void __launch_bounds__(256) k_check(Cell<real> c, int zper, double *p
     acc.zero();
     const int z0 = blockIdx.z * zper, z1 = min(c.nz, z0 + zper);
     const XLink xl = chunk_links<VEC>(c, xv, tx, bx);
-    for (int z = z0; z < z1; z++) node_update<real, VEC, MODE, 0, ST>(c, tab, xv, y, z, active, xl, acc, qout, qscale);
+    for (int z = z0; z < z1; z++)
+        node_update<real, VEC, MODE, 0, ST>(c, tab, xv, y, z, active, xl, acc, qout, qscale, [&](const real *&) {
+            if (!staged) table_commit(c, tab, tp);
+            staged = true;
+        });
     const long long b = ((long long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-    block_reduce_store(acc, partials + b * NRED);
+    if constexpr (observes(MODE)) block_reduce_store(acc, partials + b * NRED);
 }
 
-__global__ void __launch_bounds__(256) k_reduce(const double *__restrict__ partials, int nparts, double *final8) {
-    __shared__ double red[256][NRED];
-    const int t = threadIdx.x;
-    double v[NRED];
-    for (int k = 0; k < NRED; k++) v[k] = 0.0;
-    for (int i = t; i < nparts; i += 256)
-        for (int k = 0; k < NRED; k++) {
-            double p = partials[(long long)i * NRED + k];
-            v[k] = (k == R_RESID) ? fmax(v[k], p) : v[k] + p;
-        }
-    for (int k = 0; k < NRED; k++) red[t][k] = v[k];
-    __syncthreads();
-    for (int stride = 128; stride >= 1; stride >>= 1) {
-        if (t < stride)
-            for (int k = 0; k < NRED; k++)
-                red[t][k] = (k == R_RESID) ? fmax(red[t][k], red[t + stride][k]) : red[t][k] + red[t + stride][k];
-        __syncthreads();
-    }
-    if (t < NRED) final8[t] = red[0][t];
+// About 2048 partials: 1024 threads read them in two round trips (256 threads
+// and a tree over LDS: 5.5 us; 4.4 like this).  The sums go straight to pinned
+// host memory: the copy behind them was a launch of its own.
+__global__ void __launch_bounds__(1024) k_reduce(const double *__restrict__ partials, int nparts, double *sums) {
+    reduce_partials(partials, 0, nparts, sums);
 }
 
 // T_lin at node index i of the gradient axis: walls at -1/2 and n - 1/2
@@ -151,14 +147,16 @@ __device__ __forceinline__ double t_lin(int i, int n, double t_hot, double dT) {
     return t_hot - (i + 0.5) * dT / n;
 }
 
-template <typename real>
-__global__ void k_init(Cell<real> c, real *state, const real *t0, int flags, double t_hot, double dT) {
+// idx: unsigned where the nodes fit 31 bits; a 64-bit division takes longer
+// than the node's memory traffic
+template <typename real, typename idx>
+__global__ void __launch_bounds__(256) k_init(Cell<real> c, real *state, const real *t0, int flags, double t_hot,
+                                              double dT) {
     const long long n = c.N;
     const int ext[3] = {c.nx, c.ny, c.nz};
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-        const int x = (int)(i % c.nx);
-        const long long r = i / c.nx;
-        const int y = (int)(r % c.ny), z = (int)(r / c.ny);
+    for (idx i = (idx)blockIdx.x * blockDim.x + threadIdx.x; i < (idx)n; i += (idx)gridDim.x * blockDim.x) {
+        const idx r = i / (idx)c.nx;
+        const int x = (int)(i - r * (idx)c.nx), z = (int)(r / (idx)c.ny), y = (int)(r - (idx)z * (idx)c.ny);
         const int pos[3] = {x, y, z};
         const int g = c.gaxis;
         const double tl = t_lin(pos[g], ext[g], t_hot, dT);
@@ -181,7 +179,7 @@ __global__ void k_init(Cell<real> c, real *state, const real *t0, int flags, dou
                 else if (c.per[a]) hi = t0[i - (long long)(ext[a] - 1) * stride[a]];
                 else if (a == g) { hi = t_hot - dT; dist -= 0.5; }
                 else hi = T;
-                grad[a] = (hi - lo) / dist;
+                grad[a] = dist == 2.0 ? (hi - lo) * 0.5 : (hi - lo) / dist;
             }
             // pre-collision j = -eps tau grad T (Eq. 15); jhat = (I - tau^-1) j
             // = -eps (tau - I) grad T
@@ -207,31 +205,52 @@ __global__ void k_init(Cell<real> c, real *state, const real *t0, int flags, dou
     }
 }
 
-template <typename real>
-__global__ void k_temperature(Cell<real> c, const real *__restrict__ state, real *__restrict__ t_out, double t_hot,
-                              double dT) {
+// VEC nodes of a row per thread; idx as in k_init
+template <typename real, int VEC, typename idx>
+__global__ void __launch_bounds__(256) k_temperature(Cell<real> c, const real *__restrict__ state,
+                                                     real *__restrict__ t_out, double t_hot, double dT) {
     const long long n = c.N;
-    const int ext[3] = {c.nx, c.ny, c.nz};
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-        const int x = (int)(i % c.nx);
-        const long long r = i / c.nx;
-        const int pos[3] = {x, (int)(r % c.ny), (int)(r / c.ny)};
+    const int ext[3] = {c.nx, c.ny, c.nz}, ng = ext[c.gaxis];
+    const idx nxv = c.nx / VEC, groups = (idx)(n / VEC);
+    for (idx i = (idx)blockIdx.x * blockDim.x + threadIdx.x; i < groups; i += (idx)gridDim.x * blockDim.x) {
         // T = sum of the seven populations, in the same order for both
         // storages (moment storage rebuilds each population first)
-        real acc;
+        Vec<real, VEC> acc;
+        const real *s = state + (long long)i * VEC;
         if (!c.storage) {
-            acc = state[i];
-            for (int q = 1; q < Q; q++) acc += state[q * n + i];
+            acc = vload<real, VEC, false>(s);
+#pragma unroll
+            for (int q = 1; q < Q; q++) {
+                const Vec<real, VEC> f = vload<real, VEC, false>(s + q * n);
+#pragma unroll
+                for (int v = 0; v < VEC; v++) acc.v[v] += f.v[v];
+            }
         } else {
-            const real T = state[i];
-            acc = T * real(0.25);
+            const Vec<real, VEC> T = vload<real, VEC, false>(s);
+#pragma unroll
+            for (int v = 0; v < VEC; v++) acc.v[v] = T.v[v] * real(0.25);
+#pragma unroll
             for (int a = 1; a < 4; a++) {
-                const real z = state[a * n + i];
-                acc += gplus(T, z);
-                acc += gminus(T, z);
+                const Vec<real, VEC> z = vload<real, VEC, false>(s + a * n);
+#pragma unroll
+                for (int v = 0; v < VEC; v++) {
+                    acc.v[v] += gplus(T.v[v], z.v[v]);
+                    acc.v[v] += gminus(T.v[v], z.v[v]);
+                }
             }
         }
-        t_out[i] = (real)((double)acc + t_lin(pos[c.gaxis], ext[c.gaxis], t_hot, dT));
+        const idx r = i / nxv;
+        if (c.gaxis == 0) {
+            const int x0 = (int)(i - r * nxv) * VEC;
+#pragma unroll
+            for (int v = 0; v < VEC; v++) acc.v[v] = (real)((double)acc.v[v] + t_lin(x0 + v, ng, t_hot, dT));
+        } else {
+            const idx z = r / (idx)c.ny;
+            const double tl = t_lin((int)(c.gaxis == 1 ? r - z * (idx)c.ny : z), ng, t_hot, dT);
+#pragma unroll
+            for (int v = 0; v < VEC; v++) acc.v[v] = (real)((double)acc.v[v] + tl);
+        }
+        vstore<real, VEC, false>(t_out + (long long)i * VEC, acc);
     }
 }
 
@@ -347,8 +366,8 @@ hipError_t launch_check(const Cell<real> &c, const Launch &L, int mode, double *
     return hipGetLastError();
 }
 
-hipError_t launch_reduce(const double *partials, int nparts, double *final8, hipStream_t s) {
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(256), 0, s, partials, nparts, final8);
+hipError_t launch_reduce(const double *partials, int nparts, double *sums, hipStream_t s) {
+    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(1024), 0, s, partials, nparts, sums);
     return hipGetLastError();
 }
 
@@ -360,14 +379,27 @@ static inline int grid_1d(long long n) {
 template <typename real>
 hipError_t launch_init(const Cell<real> &c, real *state, const real *t0, int flags, double t_hot, double dT,
                        hipStream_t s) {
-    hipLaunchKernelGGL((k_init<real>), dim3(grid_1d(c.N)), dim3(256), 0, s, c, state, t0, flags, t_hot, dT);
+    const dim3 g(grid_1d(c.N)), b(256);
+    if (c.N < (1LL << 31)) hipLaunchKernelGGL((k_init<real, unsigned>), g, b, 0, s, c, state, t0, flags, t_hot, dT);
+    else hipLaunchKernelGGL((k_init<real, long long>), g, b, 0, s, c, state, t0, flags, t_hot, dT);
     return hipGetLastError();
 }
 
 template <typename real>
 hipError_t launch_temperature(const Cell<real> &c, const real *state, real *t_out, double t_hot, double dT,
                               hipStream_t s) {
-    hipLaunchKernelGGL((k_temperature<real>), dim3(grid_1d(c.N)), dim3(256), 0, s, c, state, t_out, t_hot, dT);
+    // 16 bytes per thread where whole vectors make up the rows and lie
+    // aligned (the caller's array may lie anywhere)
+    constexpr int VEC = 16 / sizeof(real);
+    const bool whole = c.nx % VEC == 0 && (((uintptr_t)state | (uintptr_t)t_out) & 15) == 0;
+    const dim3 b(256);
+    if (c.N >= (1LL << 31))
+        hipLaunchKernelGGL((k_temperature<real, 1, long long>), dim3(grid_1d(c.N)), b, 0, s, c, state, t_out, t_hot, dT);
+    else if (whole)
+        hipLaunchKernelGGL((k_temperature<real, VEC, unsigned>), dim3(grid_1d(c.N / VEC)), b, 0, s, c, state, t_out, t_hot,
+                           dT);
+    else
+        hipLaunchKernelGGL((k_temperature<real, 1, unsigned>), dim3(grid_1d(c.N)), b, 0, s, c, state, t_out, t_hot, dT);
     return hipGetLastError();
 }
 

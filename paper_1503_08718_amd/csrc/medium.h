@@ -57,12 +57,12 @@ struct mrtlbm_medium {
     void *ws = nullptr;
     size_t ws_bytes = 0;
     void *bufA = nullptr, *bufB = nullptr, *tab = nullptr;
-    double *partials = nullptr, *final8 = nullptr;
+    double *partials = nullptr;
     size_t pcap = 0;
     hipStream_t stream = nullptr;
     hipStream_t cap_stream = nullptr;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
-    double *pinned = nullptr;  // host staging for reductions
+    double *pinned = nullptr;  // host memory that the reductions write their sums to
     int device = 0;
     int cur = 0;               // state in bufA (0) or bufB (1)
     int storage = 0;           // 0: 7 populations per node, 1: 4 moments per node

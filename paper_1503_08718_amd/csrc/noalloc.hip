@@ -27,9 +27,9 @@ using namespace mrt;
 
 namespace {
 
-// check-step partials of up to this many blocks, then the final reduction
+// check-step partials of up to this many blocks
 constexpr int NOALLOC_MAX_PARTIALS = 65536;
-constexpr size_t NOALLOC_DOUBLES = (size_t)(NOALLOC_MAX_PARTIALS + 2) * NRED;
+constexpr size_t NOALLOC_DOUBLES = (size_t)NOALLOC_MAX_PARTIALS * NRED;
 constexpr int MAX_DEVICES = 64;
 
 std::mutex g_scratch_mutex;
@@ -64,7 +64,6 @@ static mrtlbm_status scratch_for(int device, double **out) {
 template <typename real>
 static mrtlbm_status solve_noalloc(mrtlbm_medium *m, double tol, mrtlbm_tol_kind kind, long long max_steps, int K,
                                    double *partials, mrtlbm_result *out) {
-    double *final8 = partials + (size_t)NOALLOC_MAX_PARTIALS * NRED;
     StopState ss;
     ss.check_vol = !has_side_flux(m);
     const double zero[NRED] = {};
@@ -78,9 +77,7 @@ static mrtlbm_status solve_noalloc(mrtlbm_medium *m, double tol, mrtlbm_tol_kind
         if (e != hipSuccess) return hip_fail(e, "step kernel");
         int nb = 0;
         e = launch_check<real>(make_cell<real>(m, cur), m->launch, 1, partials, &nb, nullptr, 0.0, m->stream);
-        if (e == hipSuccess) e = launch_reduce(partials, nb, final8, m->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(m->pinned, final8, NRED * sizeof(double), hipMemcpyDeviceToHost, m->stream);
+        if (e == hipSuccess) e = launch_reduce(partials, nb, m->pinned, m->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
         if (e != hipSuccess) return hip_fail(e, "check step");
         m->cur = cur ^ 1;
