@@ -329,6 +329,7 @@ extern "C" mrtlbm_status mrtlbm_create(int nx, int ny, int nz, const unsigned ch
     m->stream = (hipStream_t)hip_stream;
     m->launch = default_launch(m);
     m->pair = p == MRTLBM_F64 ? step2_shape<double>(nx, ny, nz, nphase) : step2_shape<float>(nx, ny, nz, nphase);
+    m->pop_pair = p == MRTLBM_F64 ? pop2_shape<double>(nx, ny, nz, nphase) : pop2_shape<float>(nx, ny, nz, nphase);
     if (!m->pair.vec) {  // a single step: 2.4 us and 5.5 or 9 us per million nodes, as the pairs' rule has it
         const double single = 2.4 + (p == MRTLBM_F64 ? 9.0 : 5.5) * 1e-6 * (double)m->N;
         m->box = p == MRTLBM_F64 ? box_shape<double>(nx, ny, nz, nphase, single)
@@ -472,11 +473,13 @@ hipError_t mrt::plain_steps(mrtlbm_medium *m, long long n, bool even, hipStream_
         }
         return hipSuccess;
     }
-    const Step2Shape &g = m->pair;
-    if (g.vec && !m->single && step2_takes<real>(make_cell<real>(m, *cur))) {
+    const Cell<real> c0 = make_cell<real>(m, *cur);
+    const bool moments = m->pair.vec && step2_takes<real>(c0), populations = m->pop_pair.vec && pop2_takes<real>(c0);
+    if (!m->single && (moments || populations)) {
         const long long pairs = even ? n / 4 * 2 : n / 2;
         for (long long i = 0; i < pairs; i++) {
-            hipError_t e = launch_step2<real>(make_cell<real>(m, *cur), g, s);
+            const Cell<real> c = make_cell<real>(m, *cur);
+            hipError_t e = moments ? launch_step2<real>(c, m->pair, s) : launch_pop2<real>(c, m->pop_pair, s);
             if (e != hipSuccess) return e;
             *cur ^= 1;
         }

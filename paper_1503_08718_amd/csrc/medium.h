@@ -71,7 +71,7 @@ struct mrtlbm_medium {
     long long steps = 0;
     bool initialised = false;
     mrt::Launch launch{4, 64, 4, 0, 0};
-    mrt::Step2Shape pair;      // how two steps per pass are cut into blocks
+    mrt::Step2Shape pair, pop_pair;  // how two steps per pass are cut into blocks, per storage
     mrt::BoxShape box;         // small cells: several steps per launch
     bool single = false;       // every step its own launch, in the shape the caller set
     std::vector<mrt::GraphEntry> graphs;

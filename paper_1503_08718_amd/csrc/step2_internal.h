@@ -28,7 +28,15 @@ Step2Shape step2_shape(int nx, int ny, int nz, int nphase);
 template <typename real>
 hipError_t launch_step2(const Cell<real> &c, const Step2Shape &g, hipStream_t s);
 
-// The same for many cells in one launch.  tiles: int4 (cell, first row, first
+// Population storage (pop2_kernels.hip): the same three.
+template <typename real>
+bool pop2_takes(const Cell<real> &c);
+template <typename real>
+Step2Shape pop2_shape(int nx, int ny, int nz, int nphase);
+template <typename real>
+hipError_t launch_pop2(const Cell<real> &c, const Step2Shape &g, hipStream_t s);
+
+// The same for many cells of moment storage in one launch.  tiles: int4 (cell, first row, first
 // plane, rows | planes << 16), one block each, rows = 0: an empty tile; the
 // table holds 8 * chunk tiles and block b takes tile (b % 8) * chunk + b / 8.
 struct Step2Batch {
