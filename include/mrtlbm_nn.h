@@ -86,6 +86,12 @@ mrtlbm_status mrtlbm_nn_mse(const float *pred, int cpred, const float *target, l
 mrtlbm_status mrtlbm_nn_adam(float *weight, const float *grad, float *m, float *v, long long count, float lr,
                              float beta1, float beta2, float eps, int t, void *w_bf16, void *stream);
 
+/* The same step on several tensors at once: arrays of `tensors` pointers and
+ * counts in host memory, read before the call returns. */
+mrtlbm_status mrtlbm_nn_adam_all(int tensors, float *const *weight, const float *const *grad, float *const *m,
+                                 float *const *v, const long long *count, float lr, float beta1, float beta2, float eps,
+                                 int t, void *const *w_bf16, void *stream);
+
 /* BF16 copy of FP32 values. */
 mrtlbm_status mrtlbm_nn_to_bf16(const float *a, long long count, void *out, void *stream);
 

@@ -144,6 +144,7 @@ def load():
         "mrtlbm_nn_up2": (I, [I, P, I, I, I, I, I, P, P]),
         "mrtlbm_nn_mse": (I, [P, I, P, LL, P, P, P, P]),
         "mrtlbm_nn_adam": (I, [P, P, P, P, LL, F, F, F, F, I, P, P]),
+        "mrtlbm_nn_adam_all": (I, [I, PP, PP, PP, PP, ctypes.POINTER(LL), F, F, F, F, I, PP, P]),
         "mrtlbm_nn_to_bf16": (I, [P, LL, P, P]),
         "mrtlbm_nn_features": (I, [P, I, I, I, P, P, P]),
         "mrtlbm_nn_target": (I, [P, I, I, I, F, P, P]),

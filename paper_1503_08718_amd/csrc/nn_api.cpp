@@ -119,7 +119,16 @@ extern "C" mrtlbm_status mrtlbm_nn_mse(const float *pred, int cpred, const float
 extern "C" mrtlbm_status mrtlbm_nn_adam(float *weight, const float *grad, float *m, float *v, long long count, float lr,
                                         float beta1, float beta2, float eps, int t, void *w_bf16, void *stream) {
     if (!weight || !grad || !m || !v || count < 0 || t < 1) return fail(MRTLBM_E_ARG, "adam: bad arguments");
-    return ret(nn_adam(weight, grad, m, v, count, lr, beta1, beta2, eps, t, w_bf16, (hipStream_t)stream), "adam");
+    return ret(nn_adam(1, &weight, &grad, &m, &v, &count, lr, beta1, beta2, eps, t, &w_bf16, (hipStream_t)stream), "adam");
+}
+
+extern "C" mrtlbm_status mrtlbm_nn_adam_all(int tensors, float *const *weight, const float *const *grad, float *const *m,
+                                            float *const *v, const long long *count, float lr, float beta1, float beta2,
+                                            float eps, int t, void *const *w_bf16, void *stream) {
+    if (tensors < 0 || t < 1 || !weight || !grad || !m || !v || !count) return fail(MRTLBM_E_ARG, "adam: bad arguments");
+    for (int k = 0; k < tensors; k++)
+        if (!weight[k] || !grad[k] || !m[k] || !v[k] || count[k] < 0) return fail(MRTLBM_E_ARG, "adam: bad arguments");
+    return ret(nn_adam(tensors, weight, grad, m, v, count, lr, beta1, beta2, eps, t, w_bf16, (hipStream_t)stream), "adam");
 }
 
 extern "C" mrtlbm_status mrtlbm_nn_to_bf16(const float *a, long long count, void *out, void *stream) {

@@ -37,8 +37,10 @@ hipError_t nn_up2(int fwd, const void *in, int n, int D, int H, int W, int c, vo
 int nn_mse_blocks(long long nvox);
 hipError_t nn_mse(const float *pred, int cpred, const float *target, long long nvox, void *dpred, float *partials,
                   hipStream_t s);
-hipError_t nn_adam(float *w, const float *g, float *m, float *v, long long n, float lr, float b1, float b2, float eps,
-                   int t, void *wb, hipStream_t s);
+// one Adam step on `count` tensors; wb (and any wb[k]) may be NULL
+constexpr int ADAM_TENSORS = 32;  // of one launch
+hipError_t nn_adam(int count, float *const *w, const float *const *g, float *const *m, float *const *v, const long long *n,
+                   float lr, float b1, float b2, float eps, int t, void *const *wb, hipStream_t s);
 hipError_t nn_to_bf16(const float *a, long long n, void *out, hipStream_t s);
 hipError_t nn_features(const uint8_t *phase, int D, int H, int W, const float *feat, void *out, hipStream_t s);
 hipError_t nn_features_resampled(const uint8_t *phase, int D, int H, int W, const float *feat, int Dc, int Hc, int Wc,

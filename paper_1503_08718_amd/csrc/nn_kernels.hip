@@ -13,6 +13,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
 
 #include "nn_device.hpp"
@@ -273,12 +274,21 @@ __global__ void __launch_bounds__(256) k_sum_splits(const float *__restrict__ pa
 
 static inline int sum_blocks(long long len) { return (int)((len + 256 / SUM_GROUPS - 1) / (256 / SUM_GROUPS)); }
 
-__global__ void k_sum_rows(const float *__restrict__ p, int rows, float scale, float *__restrict__ out) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        float acc = 0.0f;
-        for (int i = 0; i < rows; i++) acc += p[i];
-        out[0] = acc * scale;
+// sum of up to a thousand block sums by one block, in a fixed order (one thread
+// adding them one by one waited for each load: 1024 rows 47 us, 4.6 like this)
+__global__ void __launch_bounds__(256) k_sum_rows(const float *__restrict__ p, int rows, float scale,
+                                                  float *__restrict__ out) {
+    __shared__ float red[256];
+    float acc = 0.0f;
+#pragma unroll 4
+    for (int i = threadIdx.x; i < rows; i += 256) acc += p[i];
+    red[threadIdx.x] = acc;
+    __syncthreads();
+    for (int s = 128; s >= 1; s >>= 1) {
+        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+        __syncthreads();
     }
+    if (threadIdx.x == 0) out[0] = red[0] * scale;
 }
 
 // bias gradient partials: partials[s][c] = sum over the split's voxels of dy[v][c].
@@ -488,11 +498,19 @@ __global__ void __launch_bounds__(256) k_mse(const float *__restrict__ pred, int
                                              long long nvox, bf16 *__restrict__ dpred, float *__restrict__ partials) {
     __shared__ float red[256];
     float acc = 0.0f;
+    const bool wide = cpred % 8 == 0 && (reinterpret_cast<uintptr_t>(dpred) & 15) == 0;  // 16 bytes per store
     for (long long v = blockIdx.x * 256LL + threadIdx.x; v < nvox; v += (long long)gridDim.x * 256) {
         const float d = pred[v * cpred] - target[v];
         acc += d * d;
-        dpred[v * cpred] = (bf16)(2.0f * d / (float)nvox);
-        for (int ch = 1; ch < cpred; ch++) dpred[v * cpred + ch] = (bf16)0.0f;
+        const bf16 first = (bf16)(2.0f * d / (float)nvox);
+        if (wide) {
+            bf16x8 o = zero8();
+            o[0] = first;
+            for (int ch = 0; ch < cpred; ch += 8, o[0] = (bf16)0.0f) *reinterpret_cast<bf16x8 *>(dpred + v * cpred + ch) = o;
+        } else {
+            dpred[v * cpred] = first;
+            for (int ch = 1; ch < cpred; ch++) dpred[v * cpred + ch] = (bf16)0.0f;
+        }
     }
     red[threadIdx.x] = acc;
     __syncthreads();
@@ -503,11 +521,34 @@ __global__ void __launch_bounds__(256) k_mse(const float *__restrict__ pred, int
     if (threadIdx.x == 0) partials[blockIdx.x] = red[0];
 }
 
-// Adam on FP32 master weights; also writes the BF16 copy used by the kernels
-__global__ void k_adam(float *__restrict__ w, const float *__restrict__ g, float *__restrict__ m, float *__restrict__ v,
-                       long long n, float lr, float b1, float b2, float eps, float c1, float c2,
-                       bf16 *__restrict__ wb) {
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
+// Adam on FP32 master weights; also writes the BF16 copy used by the kernels.
+// One launch for up to ADAM_TENSORS tensors: most of a network's are so small
+// that a launch of their own takes longer than their work (30 tensors of the
+// warm-start network: 81 -> 12 us).  Block b works on the tensor whose range of
+// blocks holds it, ADAM_CHUNK values.
+struct AdamTensors {
+    float *w[ADAM_TENSORS];
+    const float *g[ADAM_TENSORS];
+    float *m[ADAM_TENSORS], *v[ADAM_TENSORS];
+    bf16 *wb[ADAM_TENSORS];
+    long long n[ADAM_TENSORS];
+    unsigned first[ADAM_TENSORS + 1];  // first block
+    int count;
+};
+
+constexpr int ADAM_CHUNK = 1024;
+
+__global__ void __launch_bounds__(256) k_adam(AdamTensors a, float lr, float b1, float b2, float eps, float c1, float c2) {
+    int k = 0;
+    while (k + 1 < a.count && blockIdx.x >= a.first[k + 1]) k++;
+    float *w = a.w[k], *m = a.m[k], *v = a.v[k];
+    const float *g = a.g[k];
+    bf16 *wb = a.wb[k];
+    const long long n = a.n[k], base = (long long)(blockIdx.x - a.first[k]) * ADAM_CHUNK + threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < ADAM_CHUNK / 256; u++) {
+        const long long i = base + u * 256;
+        if (i >= n) break;
         const float gi = g[i];
         const float mi = b1 * m[i] + (1.0f - b1) * gi;
         const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
@@ -629,6 +670,77 @@ __global__ void k_to_temperature(const float *__restrict__ pred, int cpred, int 
         const float t = (1.0f - ((float)x + 0.5f) / (float)W) + acc / scale;
         T[v] = t;
         if (!(t >= -margin && t <= 1.0f + margin)) nbad++;
+    }
+    // per-thread counts summed on the host side through a block reduction
+    __shared__ int red[256];
+    red[threadIdx.x] = nbad;
+    __syncthreads();
+    for (int s = 128; s >= 1; s >>= 1) {
+        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) bad[blockIdx.x] = red[0];
+}
+
+// The same by tiles of TEMP_X x TEMP_Y x TEMP_Z voxels, whose coarse values are
+// first staged in LDS: eight voxels share a coarse value, and in pred each lies
+// on a line of its own (64 bytes apart for 16 channels), so that gathering them
+// for every voxel kept the address units busy.  64^3 to 128^3: 33.8 -> 13.9 us.
+constexpr int TEMP_X = 64, TEMP_Y = 4, TEMP_Z = 4, TEMP_LDS = 4096;
+
+__device__ __forceinline__ float coarse_at(int i, float r) { return ((float)i + 0.5f) * r - 0.5f; }
+
+__global__ void __launch_bounds__(256) k_to_temperature_tile(const float *__restrict__ pred, int cpred, int Dc, int Hc,
+                                                             int Wc, int D, int H, int W, float scale, float margin,
+                                                             float *__restrict__ T, int *__restrict__ bad) {
+    __shared__ float stage[TEMP_LDS];
+    const float rx = (float)Wc / (float)W, ry = (float)Hc / (float)H, rz = (float)Dc / (float)D;
+    const unsigned ntx = (W + TEMP_X - 1) / TEMP_X, nty = (H + TEMP_Y - 1) / TEMP_Y,
+                   tiles = ntx * nty * ((D + TEMP_Z - 1) / TEMP_Z);
+    int nbad = 0;
+    for (unsigned t = blockIdx.x; t < tiles; t += gridDim.x) {
+        const unsigned tr = t / ntx;
+        const int x0 = (int)(t - tr * ntx) * TEMP_X, z0 = (int)(tr / nty) * TEMP_Z, y0 = (int)(tr % nty) * TEMP_Y;
+        // the coarse range of the tile, before wrapping and clamping
+        const int lx = (int)floorf(coarse_at(x0, rx)), ly = (int)floorf(coarse_at(y0, ry)),
+                  lz = (int)floorf(coarse_at(z0, rz));
+        const int nx = (int)floorf(coarse_at(min(x0 + TEMP_X, W) - 1, rx)) + 2 - lx,
+                  ny = (int)floorf(coarse_at(min(y0 + TEMP_Y, H) - 1, ry)) + 2 - ly,
+                  nz = (int)floorf(coarse_at(min(z0 + TEMP_Z, D) - 1, rz)) + 2 - lz;
+        __syncthreads();  // the last tile's values are used up
+        for (int i = threadIdx.x; i < nx * ny * nz; i += 256) {
+            const int r = i / nx;
+            int ix = lx + i - r * nx, iz = lz + r / ny, iy = ly + r % ny;
+            ix = min(max(ix, 0), Wc - 1);
+            iy = iy < 0 ? iy + Hc : (iy >= Hc ? iy - Hc : iy);
+            iz = iz < 0 ? iz + Dc : (iz >= Dc ? iz - Dc : iz);
+            stage[i] = pred[(((long long)iz * Hc + iy) * Wc + ix) * cpred];
+        }
+        __syncthreads();
+        const int x = x0 + (int)(threadIdx.x % TEMP_X), y = y0 + (int)(threadIdx.x / TEMP_X);
+        if (x < W && y < H) {
+            const float cx = coarse_at(x, rx), cy = coarse_at(y, ry);
+            const float fx = floorf(cx), fy = floorf(cy);
+            const float tx = cx - fx, ty = cy - fy;
+            const float lin = 1.0f - ((float)x + 0.5f) / (float)W;
+            for (int z = z0; z < min(z0 + TEMP_Z, D); z++) {
+                const float cz = coarse_at(z, rz), fz = floorf(cz), tz = cz - fz;
+                const float *st = stage + (((int)fz - lz) * ny + (int)fy - ly) * nx + (int)fx - lx;
+                float acc = 0.0f;
+#pragma unroll
+                for (int dz = 0; dz < 2; dz++)
+#pragma unroll
+                    for (int dy = 0; dy < 2; dy++)
+#pragma unroll
+                        for (int dx = 0; dx < 2; dx++) {
+                            const float wgt = (dx ? tx : 1.0f - tx) * (dy ? ty : 1.0f - ty) * (dz ? tz : 1.0f - tz);
+                            acc += wgt * st[(dz * ny + dy) * nx + dx];
+                        }
+                const float v = lin + acc / scale;
+                T[((unsigned)z * H + y) * (unsigned)W + x] = v;
+                if (!(v >= -margin && v <= 1.0f + margin)) nbad++;
+            }
+        }
     }
     // per-thread counts summed on the host side through a block reduction
     __shared__ int red[256];
@@ -815,7 +927,7 @@ hipError_t nn_up2(int fwd, const void *in, int n, int D, int H, int W, int c, vo
 }
 
 hipError_t nn_sum_rows(const float *p, int rows, float scale, float *out, hipStream_t s) {
-    hipLaunchKernelGGL(k_sum_rows, dim3(1), dim3(64), 0, s, p, rows, scale, out);
+    hipLaunchKernelGGL(k_sum_rows, dim3(1), dim3(256), 0, s, p, rows, scale, out);
     return hipGetLastError();
 }
 
@@ -828,11 +940,34 @@ hipError_t nn_mse(const float *pred, int cpred, const float *target, long long n
     return hipGetLastError();
 }
 
-hipError_t nn_adam(float *w, const float *g, float *m, float *v, long long n, float lr, float b1, float b2, float eps,
-                   int t, void *wb, hipStream_t s) {
-    float c1 = 1.0f - powf(b1, (float)t), c2 = 1.0f - powf(b2, (float)t);
-    hipLaunchKernelGGL(k_adam, dim3(g1(n)), dim3(256), 0, s, w, g, m, v, n, lr, b1, b2, eps, c1, c2, (bf16 *)wb);
-    return hipGetLastError();
+hipError_t nn_adam(int count, float *const *w, const float *const *g, float *const *m, float *const *v, const long long *n,
+                   float lr, float b1, float b2, float eps, int t, void *const *wb, hipStream_t s) {
+    const float c1 = 1.0f - powf(b1, (float)t), c2 = 1.0f - powf(b2, (float)t);
+    for (int k0 = 0; k0 < count;) {
+        AdamTensors a;
+        a.count = 0;
+        unsigned blocks = 0;
+        for (; k0 < count && a.count < ADAM_TENSORS; k0++) {
+            const long long nb = (n[k0] + ADAM_CHUNK - 1) / ADAM_CHUNK;
+            if (nb >= (1LL << 31)) return hipErrorInvalidValue;
+            if (a.count && blocks + nb >= (1LL << 31)) break;
+            if (nb == 0) continue;
+            const int i = a.count++;
+            a.w[i] = w[k0];
+            a.g[i] = g[k0];
+            a.m[i] = m[k0];
+            a.v[i] = v[k0];
+            a.wb[i] = wb ? (bf16 *)wb[k0] : nullptr;
+            a.n[i] = n[k0];
+            a.first[i] = blocks;
+            blocks += (unsigned)nb;
+        }
+        if (!a.count) break;
+        hipLaunchKernelGGL(k_adam, dim3(blocks), dim3(256), 0, s, a, lr, b1, b2, eps, c1, c2);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t nn_to_bf16(const float *a, long long n, void *out, hipStream_t s) {
@@ -867,7 +1002,17 @@ int nn_temp_blocks(long long n) { return g1(n) > 2048 ? 2048 : g1(n); }
 hipError_t nn_to_temperature(const float *pred, int cpred, int Dc, int Hc, int Wc, int D, int H, int W, float scale,
                              float margin, float *T, int *bad, hipStream_t s) {
     const long long n = (long long)D * H * W;
-    if (n < (1LL << 31))
+    // a tile's coarse range has to fit: two values and one for every 1 / r
+    // voxels of each axis, one more for the rounding (any cell coarser than about
+    // three times finer than the grid does)
+    auto span = [](int tile, int fine, int coarse) {
+        return (long long)std::ceil((double)std::min(tile, fine) * coarse / fine) + 3;
+    };
+    const long long range = span(TEMP_X, W, Wc) * span(TEMP_Y, H, Hc) * span(TEMP_Z, D, Dc);
+    if (n < (1LL << 31) && range <= TEMP_LDS)
+        hipLaunchKernelGGL(k_to_temperature_tile, dim3(nn_temp_blocks(n)), dim3(256), 0, s, pred, cpred, Dc, Hc, Wc, D, H,
+                           W, scale, margin, T, bad);
+    else if (n < (1LL << 31))
         hipLaunchKernelGGL(k_to_temperature<unsigned>, dim3(nn_temp_blocks(n)), dim3(256), 0, s, pred, cpred, Dc, Hc, Wc, D,
                            H, W, scale, margin, T, bad);
     else

@@ -277,12 +277,14 @@ class Net:
 
     def adam(self, lr=1e-3, b1=0.9, b2=0.999, eps=1e-8):
         self.t += 1
-        for name, _, _, _ in LAYERS:
-            check(self.L.mrtlbm_nn_adam(_p(self.w32[name]), _p(self.gw[name]), _p(self.mw[name]), _p(self.vw[name]),
-                                        self.w32[name].numel(), lr, b1, b2, eps, self.t, _p(self.wbf[name]),
+        groups = ((self.w32, self.gw, self.mw, self.vw, self.wbf), (self.b32, self.gb, self.mb, self.vb, None))
+        w, g, m, v, wb = ([None if d is None else d[name].data_ptr() for name, _, _, _ in LAYERS for d in ds]
+                          for ds in zip(*groups))
+        count = [d[0][name].numel() for name, _, _, _ in LAYERS for d in groups]
+        n = len(count)
+        ptrs = [(ctypes.c_void_p * n)(*p) for p in (w, g, m, v, wb)]
+        check(self.L.mrtlbm_nn_adam_all(n, *ptrs[:4], (ctypes.c_longlong * n)(*count), lr, b1, b2, eps, self.t, ptrs[4],
                                         self.stream))
-            check(self.L.mrtlbm_nn_adam(_p(self.b32[name]), _p(self.gb[name]), _p(self.mb[name]), _p(self.vb[name]),
-                                        self.b32[name].numel(), lr, b1, b2, eps, self.t, None, self.stream))
 
     def set_input(self, b: int, phase_dev: torch.Tensor, feat_dev: torch.Tensor, shape=None):
         """Features of sample b of the batch from a cell of shape (z, y, x)
