@@ -12,9 +12,9 @@
 // L1, which bound it.  The products and their order (tap, then channel, in
 // chunks of 32) are those of k_conv_fwd: the results agree bit for bit.
 //
-// Gathered -> staged (MI355X): 16 -> 16 channels on 64^3 voxels 26.8 -> 15.4 us,
-// on 4 x 64^3 89 -> 42; 32 -> 16 on 64^3 53.7 -> 18.6; 64 -> 64 on 16^3 29.8 -> 12.0;
-// 128 -> 128 on 8^3 38.1 -> 20; one inference of a 128^3 cell 0.58 -> 0.33 ms.
+// Gathered -> staged (MI355X): 16 -> 16 channels on 4 x 64^3 voxels 89 -> 40.7 us,
+// on 64^3 26.8 -> 14; 32 -> 16 on 64^3 53.7 -> 17; 64 -> 64 on 16^3 29.8 -> 11;
+// 128 -> 128 on 8^3 38.1 -> 18.8; one inference of a 128^3 cell 0.58 -> 0.30 ms.
 // LDS reads (one per product at 16 output channels) and, on the coarse
 // levels, the chain of 54 or 108 dependent products bound it now.
 #include "nn_tile.hpp"
@@ -24,7 +24,7 @@ namespace mrt {
 // positions of a plane of 8 channels, a zero vector behind its voxels.  The
 // large tile's planes lie a multiple of 16 apart, as neighbouring quarters of
 // a wave read neighbouring ones; the small tiles, where the LDS is not what a
-// launch waits for, gain nothing from that (64 -> 64 on 16^3 10.8 us, 11.1 with it)
+// launch waits for, gain nothing from that (64 -> 64 on 16^3 10.8 us back to back, 11.1 with it)
 template <int TY, int TZ>
 constexpr int conv_plane() {
     typedef Tile<TY, TZ> T;
@@ -63,20 +63,27 @@ __global__ void __launch_bounds__(256) k_conv_tile(const bf16 *__restrict__ in, 
         for (int r = 0; r < 4; r++) b4[j][r] = bias ? bias[n0 + j * 16 + quad * 4 + r] : 0.0f;
 
     // the halo tile; neighbouring threads take neighbouring channel groups
-    constexpr int ITEMS = T::HALO * GROUPS, PER = (ITEMS + 255) / 256;
-    constexpr int BATCH = PER < 8 ? PER : 8;  // loads in flight per thread
-    for (int i0 = 0; i0 < PER; i0 += BATCH) {
-        bf16x8 v[BATCH];
+    {
+        typedef typename T::template Stage<GROUPS> St;
+        const St st;
+        const int x = st.takes ? tile.column(g, st.hx) : -1, lane_row = tile.row(g, lane);
+        const bf16 *from = in + (long long)max(x, 0) * CIN + st.cg * 8;
+        bf16x8 *to = lds + st.cg * PLANE + st.l0 * PITCH + st.hx;
+        constexpr int BATCH = St::PASSES < 12 ? St::PASSES : 12;  // loads in flight per thread
 #pragma unroll
-        for (int u = 0; u < BATCH; u++) {
-            const int i = (i0 + u) * 256 + threadIdx.x;
-            const int p = i < ITEMS ? tile.source(g, i / GROUPS) : -1;
-            v[u] = p >= 0 ? *reinterpret_cast<const bf16x8 *>(in + (long long)p * CIN + i % GROUPS * 8) : zero8();
-        }
+        for (int i0 = 0; i0 < St::PASSES; i0 += BATCH) {
+            bf16x8 v[BATCH];
 #pragma unroll
-        for (int u = 0; u < BATCH; u++) {
-            const int i = (i0 + u) * 256 + threadIdx.x;
-            if (i < ITEMS) lds[i % GROUPS * PLANE + T::place(i / GROUPS)] = v[u];
+            for (int u = 0; u < BATCH; u++) {
+                if (i0 + u >= St::PASSES) break;
+                const int r = __shfl(lane_row, st.line(i0 + u), 64);
+                v[u] = r >= 0 && x >= 0 ? *reinterpret_cast<const bf16x8 *>(from + (long long)r * CIN) : zero8();
+            }
+#pragma unroll
+            for (int u = 0; u < BATCH; u++) {
+                if (i0 + u >= St::PASSES) break;
+                if (st.stores(i0 + u)) to[(i0 + u) * St::AT_ONCE * PITCH] = v[u];
+            }
         }
     }
     if (threadIdx.x < GROUPS) lds[threadIdx.x * PLANE + T::SPAN] = zero8();

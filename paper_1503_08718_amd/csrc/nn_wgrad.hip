@@ -8,7 +8,7 @@
 // from there with the transposing LDS read (16 lanes take a 4 x 16 block and
 // each gets one column of it).  The kernel before staged a transposed copy of
 // the x columns for each tap, two bytes at a time: 27 gathers and 8 LDS writes
-// per 16 bytes.  16 -> 16 channels on 4 x 64^3 voxels: 317 -> 48 us, and 41 us
+// per 16 bytes.  16 -> 16 channels on 4 x 64^3 voxels: 317 -> 44 us, and 41 us
 // for the bias gradient of its own kernel -> none; 32 -> 16 there 355 -> 84;
 // 64 -> 64 on 4 x 16^3 38.6 -> 24.4; a training iteration 4.37 -> 2.02 ms.  LDS
 // reads bound it (two per product at 16 output channels).
@@ -93,16 +93,20 @@ __global__ void __launch_bounds__(256, 2) k_wgrad_tile(const bf16 *__restrict__ 
     const int col = CIN == 8 ? (j & 1) * 8 : (j & 3) * 8;  // bytes
     const int row = j >> 2;
 
-    constexpr int XG = CB / 8, XITEMS = WTile::HALO * XG, XPER = (XITEMS + 255) / 256;
+    typedef WTile::Stage<CB / 8> St;
+    constexpr int XPER = St::PASSES;
+    const St st;
+    char *xto = xs + (CB < 16 ? 0 : st.cg / 2 * XPLANE + st.cg % 2 * 16) + (st.l0 * WG_PITCH + st.hx) * XLINE;
     constexpr int DG = CO / 8, DITEMS = WG_VOX * DG, DPER = DITEMS / 256;
     for (int t0 = split; t0 < ntiles; t0 += nsplits) {
         const WTile tile(g, (unsigned)t0);
+        const int xc = st.takes ? tile.column(g, st.hx) : -1, lane_row = tile.row(g, lane);
+        const bf16 *from = x + (long long)max(xc, 0) * CIN + cig * CB + st.cg * 8;
         bf16x8 xv[XPER], dv[DPER];
 #pragma unroll
         for (int u = 0; u < XPER; u++) {
-            const int i = u * 256 + threadIdx.x;
-            const int p = i < XITEMS ? tile.source(g, i / XG) : -1;
-            xv[u] = p >= 0 ? *reinterpret_cast<const bf16x8 *>(x + (long long)p * CIN + cig * CB + i % XG * 8) : zero8();
+            const int r = __shfl(lane_row, st.line(u), 64);
+            xv[u] = r >= 0 && xc >= 0 ? *reinterpret_cast<const bf16x8 *>(from + (long long)r * CIN) : zero8();
         }
 #pragma unroll
         for (int u = 0; u < DPER; u++) {
@@ -112,11 +116,8 @@ __global__ void __launch_bounds__(256, 2) k_wgrad_tile(const bf16 *__restrict__ 
         }
         __syncthreads();  // the tile before is read
 #pragma unroll
-        for (int u = 0; u < XPER; u++) {
-            const int i = u * 256 + threadIdx.x, c = i % XG;
-            if (i < XITEMS)
-                *reinterpret_cast<bf16x8 *>(xs + (CB < 16 ? 0 : c / 2 * XPLANE) + WTile::place(i / XG) * XLINE + (CB < 16 ? 0 : c % 2 * 16)) = xv[u];
-        }
+        for (int u = 0; u < XPER; u++)
+            if (st.stores(u)) *reinterpret_cast<bf16x8 *>(xto + u * St::AT_ONCE * WG_PITCH * XLINE) = xv[u];
 #pragma unroll
         for (int u = 0; u < DPER; u++) {
             const int i = u * 256 + threadIdx.x, c = i % DG;
