@@ -222,15 +222,17 @@ static double box_updates(int nx, int ty, int tz, int S) {
 // latency, the chain of sums) and BOX_T2 for each node update of the blocks
 // that share a CU.  Measured at 16^3 FP64 with (S, ty, tz): (2, 1, 1) 3.7, (3, 2, 2)
 // 5.2, (4, 2, 2) 6.8, (4, 4, 4) 9.0, (5, 2, 2) 9.1; at 32^3 FP32 (2, 2, 2) 4.3.
-// On top, the boxes' loads at 3.7 TB/s, which the overlapping halos need: a
-// wider FP64 cell (88 x 64 x 16) took 8.8 with (2, 2, 2), 3.7 of them for
-// 20 MB, and is faster in single steps.
+// On top, what the boxes load beyond the 4 MB of those cells, at 3.7 TB/s, which
+// the overlapping halos need: a wider FP64 cell (88 x 64 x 16) took 8.8 with
+// (2, 2, 2), 3.7 of them for 20 MB, and is faster in single steps.  Counted from
+// the first byte, 16^3 FP64 got (3, 2, 2) and 1.82 us per step instead of 1.71.
+// The model errs by a tenth, so a box has to promise that much.
 constexpr double BOX_T0 = 2.2, BOX_T1 = 0.7, BOX_T2 = 0.0009;
 
 template <typename real>
 BoxShape box_shape(int nx, int ny, int nz, int nphase, double other) {
     BoxShape best;
-    double tmin = 0.95 * other;
+    double tmin = 0.9 * other;
     const long long N = (long long)nx * ny * nz;
     if (N > (1 << 19) || ny < 2 || nz < 2) return best;
     for (int S = 2; S <= 8 && S <= ny && S <= nz; S++)
@@ -245,7 +247,7 @@ BoxShape box_shape(int nx, int ny, int nz, int nphase, double other) {
                 const double blocks = (double)((ny + ty - 1) / ty) * ((nz + tz - 1) / tz);
                 const double occ = std::min(1024 / threads, (int)(BOX_LDS / lds));
                 const double k = std::min(occ, std::ceil(blocks / BOX_CUS)), rounds = std::ceil(blocks / (BOX_CUS * occ));
-                const double bytes = blocks * first * sizeof(real) * (sizeof(real) == 8 ? 7 : 4);
+                const double bytes = std::max(0.0, blocks * first * sizeof(real) * (sizeof(real) == 8 ? 7 : 4) - 4e6);
                 const double t =
                     (BOX_T0 + rounds * (S * BOX_T1 + k * BOX_T2 * box_updates(nx, ty, tz, S)) + bytes / 3.7e6) / S;
                 if (t < tmin) {
