@@ -175,8 +175,12 @@ template <typename real>
 Step2Batch step2_batch_shape(const Step2Extent *cells, int n) {
     Step2Batch g;
     int vec = 0;
+    bool narrow = false;  // some row is no multiple of 16 bytes: the single step takes fewer nodes per thread
     double nodes = 0;
-    for (int i = 0; i < n; i++) vec = std::max(vec, step2_vec(sizeof(real), cells[i].nx));
+    for (int i = 0; i < n; i++) {
+        vec = std::max(vec, step2_vec(sizeof(real), cells[i].nx));
+        narrow = narrow || cells[i].nx % (sizeof(real) == 4 ? 4 : 2) != 0;
+    }
     g.gaxis = cells[0].gaxis;
     for (int i = 0; i < n; i++) {
         const Step2Extent &c = cells[i];
@@ -191,7 +195,12 @@ Step2Batch step2_batch_shape(const Step2Extent *cells, int n) {
     g.state_bytes = (size_t)(8.0 * sizeof(real) * nodes);
     const int maxw = (sizeof(real) * vec > 16 ? 512 : 1024) / 64;
     const double per_wave = sizeof(real) == 8 && vec == 2 ? 0.48 : 0.84;
-    double tmin = 2.0 * (2.4 + (sizeof(real) == 4 ? 5.5 : 9.0) * 1e-6 * nodes);
+    // two single steps: 4.4 us each (a block first reads its tile and its cell) and
+    // 6.5 or 9 us per million nodes; all cells share the vector of the narrowest,
+    // twice as long with 2 or 1 nodes (FP32: 4 cells of 32..64, 0.3 M nodes 8.7 us;
+    // 12 of 64..128, 9.4 M 66; 8 of 46..88 x 32 x 32 in vectors of 2, 0.53 M 10.4; 12
+    // of 24..64 with odd rows, 0.71 M 12.2)
+    double tmin = 2.0 * (4.4 + (sizeof(real) == 4 ? 6.5 : 9.0) * (narrow ? 1.9 : 1.0) * 1e-6 * nodes);
     Step2Batch best;
     g.vec = vec;
     for (int w = 1; w <= maxw; w++) {
