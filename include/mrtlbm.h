@@ -179,7 +179,9 @@ mrtlbm_status mrtlbm_set_scale(mrtlbm_medium *m, double dmax);
  * differences of t0 (Eq. 15 read backwards).  Resets the step counter. */
 mrtlbm_status mrtlbm_init(mrtlbm_medium *m, const void *t0_dev, int flags);
 
-/* Advance nsteps collide-and-stream steps (Eqs. 5, 8, 21, 23-25); async. */
+/* Advance nsteps collide-and-stream steps (Eqs. 5, 8, 21, 23-25); async.
+ * Captured into a caller's graph, an even number (below 128) advances the
+ * state by as much at every replay; the step counter counts the call alone. */
 mrtlbm_status mrtlbm_step(mrtlbm_medium *m, long long nsteps);
 
 /*

@@ -456,14 +456,15 @@ extern "C" mrtlbm_status mrtlbm_set_launch(mrtlbm_medium *m, const mrtlbm_launch
 // stepping
 // ---------------------------------------------------------------------------
 
-// n steps, in pairs or more per launch where the medium takes them; even: as
-// many launches as n in parity, so that the buffers have changed places as n
-// single steps would have them (a captured graph is replayed from one buffer)
+// n steps, in pairs or more per launch where the medium takes them, in as many
+// launches as n in parity: the buffers have then changed places as n single
+// steps would have them, which graphs rely on, the medium's own and a caller's
+// (they start from one buffer at every replay)
 template <typename real>
-hipError_t mrt::plain_steps(mrtlbm_medium *m, long long n, bool even, hipStream_t s, int *cur) {
+hipError_t mrt::plain_steps(mrtlbm_medium *m, long long n, hipStream_t s, int *cur) {
     if (!m->single && m->box.steps && n > 1 && box_takes<real>(make_cell<real>(m, *cur))) {
         long long launches = (n + m->box.steps - 1) / m->box.steps;
-        if (even && (launches ^ n) & 1) launches++;
+        if ((launches ^ n) & 1) launches++;
         for (long long i = 0; i < launches; i++) {
             const int steps = (int)((n + launches - 1 - i) / (launches - i));
             hipError_t e = launch_box<real>(make_cell<real>(m, *cur), m->box, steps, s);
@@ -476,7 +477,7 @@ hipError_t mrt::plain_steps(mrtlbm_medium *m, long long n, bool even, hipStream_
     const Cell<real> c0 = make_cell<real>(m, *cur);
     const bool moments = m->pair.vec && step2_takes<real>(c0), populations = m->pop_pair.vec && pop2_takes<real>(c0);
     if (!m->single && (moments || populations)) {
-        const long long pairs = even ? n / 4 * 2 : n / 2;
+        const long long pairs = n / 4 * 2;
         for (long long i = 0; i < pairs; i++) {
             const Cell<real> c = make_cell<real>(m, *cur);
             hipError_t e = moments ? launch_step2<real>(c, m->pair, s) : launch_pop2<real>(c, m->pop_pair, s);
@@ -492,8 +493,8 @@ hipError_t mrt::plain_steps(mrtlbm_medium *m, long long n, bool even, hipStream_
     }
     return hipSuccess;
 }
-template hipError_t mrt::plain_steps<float>(mrtlbm_medium *, long long, bool, hipStream_t, int *);
-template hipError_t mrt::plain_steps<double>(mrtlbm_medium *, long long, bool, hipStream_t, int *);
+template hipError_t mrt::plain_steps<float>(mrtlbm_medium *, long long, hipStream_t, int *);
+template hipError_t mrt::plain_steps<double>(mrtlbm_medium *, long long, hipStream_t, int *);
 
 template <typename real>
 static hipError_t check_step(mrtlbm_medium *m, int mode, hipStream_t s, int *cur, void *qout, double qscale) {
@@ -521,7 +522,7 @@ static mrtlbm_status get_graph(mrtlbm_medium *m, int K, bool with_check, hipGrap
     if (!m->cap_stream) HIPCHK(hipStreamCreateWithFlags(&m->cap_stream, hipStreamNonBlocking));
     HIPCHK(hipStreamBeginCapture(m->cap_stream, hipStreamCaptureModeThreadLocal));
     int cur = m->cur;
-    hipError_t e = plain_steps<real>(m, with_check ? K - 1 : K, true, m->cap_stream, &cur);
+    hipError_t e = plain_steps<real>(m, with_check ? K - 1 : K, m->cap_stream, &cur);
     if (e == hipSuccess && with_check) e = check_step<real>(m, 1, m->cap_stream, &cur, nullptr, 0.0);
     hipGraph_t graph = nullptr;
     hipError_t e2 = hipStreamEndCapture(m->cap_stream, &graph);
@@ -553,7 +554,7 @@ static mrtlbm_status do_steps(mrtlbm_medium *m, long long nsteps) {
         for (; done + G <= nsteps; done += G) HIPCHK(hipGraphLaunch(ge, m->stream));
     }
     int cur = m->cur;
-    HIPCHK(plain_steps<real>(m, nsteps - done, false, m->stream, &cur));
+    HIPCHK(plain_steps<real>(m, nsteps - done, m->stream, &cur));
     m->cur = cur;
     m->steps += nsteps;
     return MRTLBM_OK;
@@ -714,7 +715,7 @@ static mrtlbm_status do_solve(mrtlbm_medium *m, double tol, mrtlbm_tol_kind kind
             m->steps += K;
         } else {
             int cur = m->cur;
-            HIPCHK(plain_steps<real>(m, left - 1, false, m->stream, &cur));
+            HIPCHK(plain_steps<real>(m, left - 1, m->stream, &cur));
             HIPCHK(check_step<real>(m, 1, m->stream, &cur, nullptr, 0.0));
             m->cur = cur;
             m->steps += left;

@@ -84,7 +84,7 @@ template <typename real>
 Cell<real> make_cell(const mrtlbm_medium *m, int cur);
 void drop_graphs(mrtlbm_medium *m);
 template <typename real>
-hipError_t plain_steps(mrtlbm_medium *m, long long n, bool even, hipStream_t s, int *cur);
+hipError_t plain_steps(mrtlbm_medium *m, long long n, hipStream_t s, int *cur);
 void fill_result(const mrtlbm_medium *m, const double *f, mrtlbm_result *out);
 int stop_rule(StopState &ss, const mrtlbm_result &r, double tol, mrtlbm_tol_kind kind);
 bool has_side_flux(const mrtlbm_medium *m);
