@@ -256,6 +256,12 @@ mrtlbm_status mrtlbm_state_set(mrtlbm_medium *m, const void *f_dev, long long st
 /* Scale s, steps taken, and the launch shape in use. */
 mrtlbm_status mrtlbm_info(const mrtlbm_medium *m, double *scale, long long *steps, mrtlbm_launch *launch);
 
+/* The kernel that steps of the medium run in as it stands (sides, storage and
+ * block shape), and the most steps that one launch of it takes: "k_step" (1),
+ * "k_step2" or "k_pop2" (2) or "k_box" (2 to 8); what these leave over runs in
+ * k_step.  steps may be NULL; NULL for a NULL medium. */
+const char *mrtlbm_step_kernel(const mrtlbm_medium *m, int *steps);
+
 /* Choose the step kernel's block shape.  NULL restores the default.  A shape
  * set here is used for every step; otherwise a launch takes several steps
  * where that is faster and the storage allows it (same results bit for bit),
@@ -303,6 +309,10 @@ void mrtlbm_set_progress(mrtlbm_progress_fn fn, void *user, double interval_s);
 
 /* Bytes of device workspace mrtlbm_batch_solve needs for these media. */
 size_t mrtlbm_batch_workspace_bytes(mrtlbm_medium *const *cells, int n);
+
+/* As mrtlbm_step_kernel for these media together: "k_batch" (1) or "k_batch2"
+ * (2); NULL for media that cannot be solved together. */
+const char *mrtlbm_batch_step_kernel(mrtlbm_medium *const *cells, int n, int *steps);
 
 /*
  * Solve n initialised media together.  Every step is one kernel launch that

@@ -120,6 +120,8 @@ def load():
         "mrtlbm_set_storage": (I, [P, I]),
         "mrtlbm_state_values": (I, [P]),
         "mrtlbm_info": (I, [P, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_longlong), LP]),
+        "mrtlbm_step_kernel": (ctypes.c_char_p, [P, ctypes.POINTER(I)]),
+        "mrtlbm_batch_step_kernel": (ctypes.c_char_p, [PP, I, ctypes.POINTER(I)]),
         "mrtlbm_set_launch": (I, [P, LP]),
         "mrtlbm_autotune": (I, [P, ctypes.c_char_p, LP]),
         "mrtlbm_load_tuned": (I, [P, ctypes.c_char_p]),

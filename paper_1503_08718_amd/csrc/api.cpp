@@ -456,13 +456,33 @@ extern "C" mrtlbm_status mrtlbm_set_launch(mrtlbm_medium *m, const mrtlbm_launch
 // stepping
 // ---------------------------------------------------------------------------
 
+template <typename real>
+Route mrt::route(const mrtlbm_medium *m) {
+    if (m->single) return Route::single;
+    const Cell<real> c = make_cell<real>(m, m->cur);
+    if (m->box.steps && box_takes<real>(c)) return Route::box;
+    if (m->pair.vec && step2_takes<real>(c)) return Route::pairs;
+    if (m->pop_pair.vec && pop2_takes<real>(c)) return Route::population_pairs;
+    return Route::single;
+}
+template Route mrt::route<float>(const mrtlbm_medium *);
+template Route mrt::route<double>(const mrtlbm_medium *);
+
+extern "C" const char *mrtlbm_step_kernel(const mrtlbm_medium *m, int *steps) {
+    if (!m) return nullptr;
+    const Route r = m->prec == MRTLBM_F64 ? route<double>(m) : route<float>(m);
+    if (steps) *steps = r == Route::single ? 1 : (r == Route::box ? m->box.steps : 2);
+    return r == Route::box ? "k_box" : (r == Route::pairs ? "k_step2" : (r == Route::single ? "k_step" : "k_pop2"));
+}
+
 // n steps, in pairs or more per launch where the medium takes them, in as many
 // launches as n in parity: the buffers have then changed places as n single
 // steps would have them, which graphs rely on, the medium's own and a caller's
 // (they start from one buffer at every replay)
 template <typename real>
 hipError_t mrt::plain_steps(mrtlbm_medium *m, long long n, hipStream_t s, int *cur) {
-    if (!m->single && m->box.steps && n > 1 && box_takes<real>(make_cell<real>(m, *cur))) {
+    const Route r = route<real>(m);
+    if (r == Route::box && n > 1) {
         long long launches = (n + m->box.steps - 1) / m->box.steps;
         if ((launches ^ n) & 1) launches++;
         for (long long i = 0; i < launches; i++) {
@@ -474,13 +494,11 @@ hipError_t mrt::plain_steps(mrtlbm_medium *m, long long n, hipStream_t s, int *c
         }
         return hipSuccess;
     }
-    const Cell<real> c0 = make_cell<real>(m, *cur);
-    const bool moments = m->pair.vec && step2_takes<real>(c0), populations = m->pop_pair.vec && pop2_takes<real>(c0);
-    if (!m->single && (moments || populations)) {
+    if (r == Route::pairs || r == Route::population_pairs) {
         const long long pairs = n / 4 * 2;
         for (long long i = 0; i < pairs; i++) {
             const Cell<real> c = make_cell<real>(m, *cur);
-            hipError_t e = moments ? launch_step2<real>(c, m->pair, s) : launch_pop2<real>(c, m->pop_pair, s);
+            hipError_t e = r == Route::pairs ? launch_step2<real>(c, m->pair, s) : launch_pop2<real>(c, m->pop_pair, s);
             if (e != hipSuccess) return e;
             *cur ^= 1;
         }

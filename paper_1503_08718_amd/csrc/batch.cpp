@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <new>
 #include <vector>
 
 #include "batch_internal.h"
@@ -114,14 +115,12 @@ void add_pair_tiles(BatchRun &B, std::vector<int4> &tiles) {
     B.pair_chunk = (int)(t.size() / 8);
 }
 
-// tiles of the active cells (contiguous per cell) and per-cell tile ranges.
+// Tiles of the active cells (contiguous per cell) and per-cell tile ranges.
 // A tile is (cell, z, y0, rows): `rows` whole rows from y0, packed over the
 // block's threads; a row longer than the block is cut into x-chunks of one
 // tile each, (cell, z, y, -1 - chunk).
 template <typename real>
-mrtlbm_status upload_tiles(BatchRun &B) {
-    std::vector<int4> tiles;
-    std::vector<int> start;
+void make_tiles(BatchRun &B, std::vector<int4> &tiles, std::vector<int> &start) {
     for (int a : B.active) {
         const mrtlbm_medium *m = B.cells[a];
         const int nxv = m->nx / B.vec;
@@ -146,6 +145,13 @@ mrtlbm_status upload_tiles(BatchRun &B) {
     }
     B.ntiles = (int)tiles.size();
     add_pair_tiles<real>(B, tiles);
+}
+
+template <typename real>
+mrtlbm_status upload_tiles(BatchRun &B) {
+    std::vector<int4> tiles;
+    std::vector<int> start;
+    make_tiles<real>(B, tiles, start);
     if ((long long)tiles.size() > B.lay.max_tiles) return fail(MRTLBM_E_WORKSPACE, "tile table overflow");
     hipError_t e = hipMemcpyAsync(B.ws + B.lay.tiles, tiles.data(), tiles.size() * sizeof(int4), hipMemcpyHostToDevice,
                                   B.stream);
@@ -236,14 +242,9 @@ mrtlbm_status run(BatchRun &B, double tol, mrtlbm_tol_kind kind, long long max_s
     return worst == 2 ? MRTLBM_NOT_CONVERGED : MRTLBM_OK;
 }
 
-// checks shared by the batched solve and its autotuner; fills B
-static mrtlbm_status prepare(BatchRun &B, mrtlbm_medium *const *cells, int n, void *workspace_dev,
-                             size_t workspace_bytes, bool need_init) {
-    BatchLayout lay;
-    if (!batch_layout(cells, n, &lay)) return fail(MRTLBM_E_ARG, "bad cell list");
-    if (!workspace_dev || workspace_bytes < lay.total)
-        return fail(MRTLBM_E_WORKSPACE, "batch workspace of %zu bytes, need %zu", workspace_bytes, lay.total);
-    if (((uintptr_t)workspace_dev) & 255) return fail(MRTLBM_E_WORKSPACE, "workspace not 256-byte aligned");
+// checks of the cells; describes the batch in B
+static mrtlbm_status describe(BatchRun &B, mrtlbm_medium *const *cells, int n, bool need_init) {
+    if (!batch_layout(cells, n, &B.lay)) return fail(MRTLBM_E_ARG, "bad cell list");
     const mrtlbm_medium *m0 = cells[0];
     int vec = m0->launch.vec, threads = m0->launch.bx * m0->launch.by, max_nphase = 1;
     for (int i = 0; i < n; i++) {
@@ -271,9 +272,21 @@ static mrtlbm_status prepare(BatchRun &B, mrtlbm_medium *const *cells, int n, vo
     B.map = m0->launch.map;
     B.storage = m0->storage;
     B.single = m0->single;
-    B.ws = (char *)workspace_dev;
-    B.lay = lay;
     B.stream = m0->stream;
+    return MRTLBM_OK;
+}
+
+// checks shared by the batched solve and its autotuner; fills B
+static mrtlbm_status prepare(BatchRun &B, mrtlbm_medium *const *cells, int n, void *workspace_dev,
+                             size_t workspace_bytes, bool need_init) {
+    BatchLayout lay;
+    if (!batch_layout(cells, n, &lay)) return fail(MRTLBM_E_ARG, "bad cell list");
+    if (!workspace_dev || workspace_bytes < lay.total)
+        return fail(MRTLBM_E_WORKSPACE, "batch workspace of %zu bytes, need %zu", workspace_bytes, lay.total);
+    if (((uintptr_t)workspace_dev) & 255) return fail(MRTLBM_E_WORKSPACE, "workspace not 256-byte aligned");
+    mrtlbm_status st = describe(B, cells, n, need_init);
+    if (st != MRTLBM_OK) return st;
+    B.ws = (char *)workspace_dev;
     B.cap = nullptr;
     hipError_t e = hipStreamCreateWithFlags(&B.cap, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipHostMalloc((void **)&B.pinned, (size_t)n * NRED * sizeof(double), hipHostMallocDefault);
@@ -315,6 +328,22 @@ static mrtlbm_status time_batch(BatchRun &B, int steps, double *ms) {
 extern "C" size_t mrtlbm_batch_workspace_bytes(mrtlbm_medium *const *cells, int n) {
     BatchLayout L;
     return batch_layout(cells, n, &L) ? L.total : 0;
+}
+
+extern "C" const char *mrtlbm_batch_step_kernel(mrtlbm_medium *const *cells, int n, int *steps) {
+    try {
+        BatchRun B;
+        if (describe(B, cells, n, false) != MRTLBM_OK) return nullptr;
+        for (int i = 0; i < n; i++) B.active.push_back(i);
+        std::vector<int4> tiles;
+        std::vector<int> start;
+        if (cells[0]->prec == MRTLBM_F64) make_tiles<double>(B, tiles, start);
+        else make_tiles<float>(B, tiles, start);
+        if (steps) *steps = B.pair.vec ? 2 : 1;
+        return B.pair.vec ? "k_batch2" : "k_batch";
+    } catch (const std::bad_alloc &) {
+        return nullptr;
+    }
 }
 
 extern "C" mrtlbm_status mrtlbm_batch_solve(mrtlbm_medium *const *cells, int n, double tol, mrtlbm_tol_kind kind,

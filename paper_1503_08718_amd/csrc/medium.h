@@ -78,6 +78,10 @@ struct mrtlbm_medium {
 };
 
 namespace mrt {
+// what a medium's steps run in; single steps for what several per launch leave over
+enum class Route { single, pairs, population_pairs, box };
+template <typename real>
+Route route(const mrtlbm_medium *m);
 bool launch_ok(const mrtlbm_medium *m, const Launch &L);
 Launch default_launch(const mrtlbm_medium *m);
 template <typename real>

@@ -127,6 +127,11 @@ class Medium:
         check(load().mrtlbm_info(self._h, ctypes.byref(s), ctypes.byref(n), ctypes.byref(L)))
         return dict(scale=s.value, steps=n.value, launch=(L.vec, L.bx, L.by, L.nt, L.map))
 
+    def step_kernel(self) -> tuple[str, int]:
+        """The kernel that the steps run in and the most steps of one launch."""
+        n = ctypes.c_int()
+        return load().mrtlbm_step_kernel(self._h, ctypes.byref(n)).decode(), n.value
+
     def autotune(self, cache_path: str | None = None):
         L = Launch()
         check(load().mrtlbm_autotune(self._h, cache_path.encode() if cache_path else None, ctypes.byref(L)))
@@ -213,6 +218,17 @@ def batch_solve(media, tol: float = 1e-4, kind="keff", max_steps: int = 10**7, c
     del ws
     out = [r.to_dict() for r in res]
     return out, _lib.STATUS[st]
+
+
+def batch_step_kernel(media) -> tuple[str, int]:
+    """The kernel that a batched solve of these media starts with and the
+    steps of one launch."""
+    n = ctypes.c_int()
+    arr = (ctypes.c_void_p * len(media))(*[m.handle.value for m in media])
+    name = load().mrtlbm_batch_step_kernel(arr, len(media), ctypes.byref(n))
+    if name is None:
+        raise ValueError("these media cannot be solved together")
+    return name.decode(), n.value
 
 
 def batch_autotune(media) -> dict:

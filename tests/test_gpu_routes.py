@@ -1,0 +1,111 @@
+"""The kernels that take several steps per launch against single steps (which a
+caller-set block shape selects), bit for bit, each on cells that are seen to
+take it: the library says which kernel a medium's steps run in."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+P, A = "periodic", "adiabatic"
+WALLS = [(0, (P, P, P)), (1, (A, P, P)), (2, (P, A, P)), (0, (P, A, A)), (2, (A, A, A))]
+K = np.array([[1.0, 1.2, 0.9, 0.1, -0.05, 0.02], [6.0, 2.0, 3.0, -0.4, 0.3, 0.5], [0.2, 0.2, 0.3, 0.0, 0.01, -0.02]])
+
+
+@pytest.fixture(scope="module")
+def api():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.fail("no HIP device")
+    from paper_1503_08718_amd import solver
+
+    return solver
+
+
+def _cell(api, shape, prec, storage, axis, sides):
+    """Medium of three random phases; a state that is that of no moments
+    where the storage can hold one."""
+    import torch
+
+    gen = torch.Generator(device="cuda").manual_seed(sum(shape))
+    dims = shape[::-1]
+    phase = torch.randint(0, 3, dims, generator=gen, device="cuda", dtype=torch.uint8)
+    g = api.Medium(phase, K, precision=prec, storage=storage).set_bc(axis, 0.8, -0.4, sides)
+    g.init(torch.rand(dims, generator=gen, device="cuda", dtype=g.dtype), flux=True)
+    if storage == "populations":
+        s = g.state_get()
+        g.state_set(s * (1 + 0.2 * torch.rand(s.shape, generator=gen, device="cuda", dtype=s.dtype)))
+    return g
+
+
+def _compare(api, shape, prec, storage, kernel, axis, sides, counts):
+    import torch
+
+    g, h = (_cell(api, shape, prec, storage, axis, sides) for _ in range(2))
+    h.set_launch(*h.info()["launch"])
+    assert g.step_kernel()[0] == kernel and h.step_kernel() == ("k_step", 1)
+    for n in counts:
+        g.step(n)
+        h.step(n)
+        assert torch.equal(g.state_get(), h.state_get()), (axis, sides, n)
+
+
+ids = lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v)  # noqa: E731
+
+
+# rows of 1, 2, 16, 32 and 64 lanes, whole and ending in a shared vector; few
+# rows, few planes
+@pytest.mark.parametrize("shape", [(4, 900, 900), (5, 1000, 701), (61, 300, 130), (64, 640, 33), (125, 201, 100),
+                                   (128, 130, 128), (253, 5, 2200), (64, 20000, 4)], ids=ids)
+def test_fp32_population_pairs(api, shape):
+    for axis, sides in WALLS:
+        _compare(api, shape, "f32", "populations", "k_pop2", axis, sides, (11,))
+
+
+# just above 256 MB of state, where pairs write past the cache: each vector
+# width, whole rows and rows that end in a shared vector, each gradient axis
+@pytest.mark.parametrize("shape,prec,storage", [
+    ((256, 256, 130), "f32", "moments"), ((253, 256, 132), "f32", "moments"),
+    ((256, 130, 130), "f64", "moments"), ((253, 130, 130), "f64", "moments"),
+    ((128, 200, 170), "f64", "moments"), ((127, 200, 170), "f64", "moments"),
+    ((256, 200, 100), "f32", "populations"), ((187, 192, 190), "f32", "populations"),
+    ((256, 100, 100), "f64", "populations"), ((253, 100, 100), "f64", "populations"),
+    ((128, 140, 140), "f64", "populations"), ((127, 140, 140), "f64", "populations")], ids=ids)
+def test_pairs_beyond_the_cache(api, shape, prec, storage):
+    values, size = (4, 7)[storage == "populations"], (4, 8)[prec == "f64"]
+    assert 2 * values * size * int(np.prod(shape)) > 256 << 20
+    for axis, sides in ((0, (P, P, A)), (1, (A, P, P)), (2, (P, P, P))):
+        _compare(api, shape, prec, storage, {"moments": "k_step2", "populations": "k_pop2"}[storage], axis, sides, (7,))
+
+
+@pytest.mark.parametrize("prec,storage", [("f32", "moments"), ("f64", "moments"), ("f64", "populations")])
+@pytest.mark.parametrize("shape", [(5, 2, 3), (64, 9, 8), (28, 28, 28), (31, 17, 9), (16, 16, 16), (13, 13, 13),
+                                   (10, 30, 30), (7, 16, 20), (8, 8, 8), (3, 20, 20)], ids=ids)
+def test_boxes(api, shape, prec, storage):
+    for axis, sides in WALLS:
+        _compare(api, shape, prec, storage, "k_box", axis, sides, (2, 7, 13))
+
+
+# small and beyond the cache, whole and ragged rows
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("axis,shapes", [
+    (0, [(64, 96, 64), (48, 64, 96), (128, 64, 64)]),
+    (1, [(75, 61, 87), (64, 50, 64), (96, 96, 40)]),
+    (2, [(200, 64, 31), (30, 64, 128), (13, 130, 200)]),
+    (0, [(64, 256, 128), (128, 192, 160), (32, 300, 300)]),
+    (1, [(75, 161, 187), (63, 350, 160), (125, 160, 150)]),
+    (2, [(256, 192, 120), (92, 164, 160)]),
+    (0, [(253, 192, 120), (91, 164, 160)])], ids=ids)
+def test_batched_pairs(api, axis, shapes, prec):
+    import torch
+
+    cells, alone = ([_cell(api, s, prec, "moments", axis, (P, A, P) if i % 2 else (P, P, A))
+                     for i, s in enumerate(shapes)] for _ in range(2))
+    assert api.batch_step_kernel(cells) == ("k_batch2", 2)
+    res, _ = api.batch_solve(cells, tol=1e-30, kind="keff", max_steps=20, check_every=10)
+    for g, h, r in zip(cells, alone, res):
+        h.set_launch(*h.info()["launch"])
+        h.step(20)
+        assert r["steps"] == 20
+        assert torch.equal(g.state_get(), h.state_get())
