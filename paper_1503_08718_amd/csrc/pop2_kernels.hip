@@ -67,9 +67,10 @@ Step2Shape pop2_shape(int nx, int ny, int nz, int nphase) {
     if (nx < vec || nx > 64 * vec || ny < 2 || nz < 2 || N * (long long)sizeof(real) >= (1LL << 31)) return best;
     const int nxv = (nx + vec - 1) / vec, rpw = 64 / nxv, len = nxv * vec, maxw = POP2_THREADS / 64;
     // two single steps: 2.4 us each and 8.6 (FP32) or 15.5 (FP64) us per million
-    // nodes (FP32 64^3 4.6, 96^3 10.7, 128^3 20.2; FP64 96^3 16.0, 128^3 35.3), which
-    // FP32 pairs beat only where that is the memory's time (192^3: 76 and 54)
-    const double single = 2.4 + (sizeof(real) == 4 ? 8.6 : 15.5) * 1e-6 * (double)N;
+    // nodes (FP32 64^3 4.6, 96^3 10.7, 128^3 20.2; FP64 96^3 16.0, 128^3 35.3), with
+    // odd rows 9 to 17 and 17 to 32 (one node per thread; FP32 123 x 102 x 137 24.3)
+    const double slope = (sizeof(real) == 4 ? 8.6 : 15.5) * (nx % 2 ? 1.3 : 1.0);
+    const double single = 2.4 + slope * 1e-6 * (double)N;
     double tmin = 0.95 * 2.0 * single;
     for (int w = 1; w <= maxw; w++) {
         int tr = std::min(w * rpw - 2, ny);
@@ -79,7 +80,11 @@ Step2Shape pop2_shape(int nx, int ny, int nz, int nphase) {
         const size_t lds = (size_t)pop2_lds_bytes(sizeof(real), tr, len, nphase);
         if (lds > (size_t)POP2_LDS) continue;
         const int waves = (tr + 2 + rpw - 1) / rpw;
-        const int occ = std::min((sizeof(real) * vec > 16 ? 8 : 12) / waves, (int)(POP2_LDS / lds));
+        // waves whose registers a SIMD holds.  Of 5 or 6 waves two share a SIMD, and a
+        // second block of them does not fit beside the first (counted as if it did,
+        // FP32 120^3 took blocks of 6 and 20.3 us per step; single 17.5, blocks of 8 15.8)
+        const int simd = sizeof(real) * vec > 16 ? 2 : 3;
+        const int occ = std::min(waves > 4 ? simd / ((waves + 3) / 4) : 4 * simd / waves, (int)(POP2_LDS / lds));
         int before = 0;
         for (int planes = nz; planes >= 1; planes--) {
             const int nchunks = (nz + planes - 1) / planes;

@@ -109,3 +109,20 @@ def test_batched_pairs(api, axis, shapes, prec):
         h.step(20)
         assert r["steps"] == 20
         assert torch.equal(g.state_get(), h.state_get())
+
+
+# blocks of 5 and 6 waves would fit once on a CU; odd rows, whose single steps
+# take one node per thread
+@pytest.mark.parametrize("shape", [(120, 120, 120), (126, 117, 117), (32, 87, 511), (123, 102, 137), (245, 8, 1265)], ids=ids)
+def test_population_route_is_the_faster(api, shape):
+    """The kernel that the rule takes is not slower than single steps (by more
+    than the times vary)."""
+    g = _cell(api, shape, "f32", "populations", 0, (P, P, P))
+    launch = g.info()["launch"]
+    best = {}
+    for _ in range(4):
+        for single in (True, False):
+            g.set_launch(*launch) if single else g.set_launch()
+            g.time_steps(64)
+            best[single] = min(best.get(single, 1e9), g.time_steps(256))
+    assert best[False] < 1.05 * best[True], best
