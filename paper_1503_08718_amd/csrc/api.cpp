@@ -854,6 +854,7 @@ extern "C" mrtlbm_status mrtlbm_autotune(mrtlbm_medium *m, const char *cache_pat
     Launch bestL = m->launch;
     double bestms = 1e300;
     const Launch saved = m->launch;
+    const bool saved_single = m->single;
     m->single = true;  // the shape is the single step's
     for (int vec : {4, 2, 1})
         for (int bx : {8, 16, 32, 64})
@@ -871,7 +872,8 @@ extern "C" mrtlbm_status mrtlbm_autotune(mrtlbm_medium *m, const char *cache_pat
                 if (st == MRTLBM_OK) st = mrtlbm_time_steps(m, n, &ms);
                 if (st != MRTLBM_OK) {
                     m->launch = saved;
-                    m->single = false;
+                    m->single = saved_single;
+                    drop_graphs(m);
                     return st;
                 }
                 if (ms < bestms) {

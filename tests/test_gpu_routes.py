@@ -126,3 +126,43 @@ def test_population_route_is_the_faster(api, shape):
             g.time_steps(64)
             best[single] = min(best.get(single, 1e9), g.time_steps(256))
     assert best[False] < 1.05 * best[True], best
+
+
+FAILED_AUTOTUNE = """
+import ctypes
+import numpy as np, torch
+from paper_1503_08718_amd import solver
+from paper_1503_08718_amd._lib import MrtlbmError
+# the HIP runtime that torch and the library share
+hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+s = torch.cuda.Stream()
+with torch.cuda.stream(s):
+    g = solver.Medium(np.zeros((96, 96, 64), np.uint8), [[1, 1, 1, 0, 0, 0]], precision="f64", storage="moments")
+    g.set_bc(0)
+    before = g.step_kernel()
+    launch = (2, 16, 8, 0, 0)
+    g.set_launch(*launch)
+    s.synchronize()
+    assert hip.hipStreamBeginCapture(ctypes.c_void_p(s.cuda_stream), 2) == 0
+    try:
+        g.autotune()
+        raise SystemExit("autotune did not fail")
+    except MrtlbmError:
+        pass
+    assert before == ("k_step2", 2), before
+    assert g.step_kernel() == ("k_step", 1) and g.info()["launch"] == launch, (g.step_kernel(), g.info())
+    print("kept", flush=True)
+"""
+
+
+def test_failed_autotune_leaves_the_callers_shape():
+    """Timing fails on a stream that is being captured (in a process of its
+    own, which ends with that capture): the shape that the caller had set
+    still holds for every step."""
+    import os
+    import subprocess
+    import sys
+
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", FAILED_AUTOTUNE], cwd=root, capture_output=True, text=True, timeout=100)
+    assert "kept" in r.stdout, r.stdout + r.stderr
