@@ -270,7 +270,9 @@ mrtlbm_status mrtlbm_set_launch(mrtlbm_medium *m, const mrtlbm_launch *launch);
 
 /* Time every admissible block shape on this medium (hip events, a few
  * steps each), keep the fastest, and record it in the text file cache_path
- * (keyed by device architecture, sizes and precision; NULL = no file).
+ * (keyed by device architecture, sizes and precision; NULL = no file).  It
+ * serves every step where it beats several steps per launch (the line in the
+ * file then ends in "single"), else the remaining single steps.
  * Clobbers the state: call before mrtlbm_init.  Synchronises. */
 mrtlbm_status mrtlbm_autotune(mrtlbm_medium *m, const char *cache_path, mrtlbm_launch *best);
 

@@ -449,6 +449,7 @@ extern "C" mrtlbm_status mrtlbm_set_launch(mrtlbm_medium *m, const mrtlbm_launch
     drop_graphs(m);
     m->launch = L;
     m->single = launch != nullptr;
+    m->tuned_single = false;
     return MRTLBM_OK;
 }
 
@@ -458,7 +459,7 @@ extern "C" mrtlbm_status mrtlbm_set_launch(mrtlbm_medium *m, const mrtlbm_launch
 
 template <typename real>
 Route mrt::route(const mrtlbm_medium *m) {
-    if (m->single) return Route::single;
+    if (m->single || m->tuned_single) return Route::single;
     const Cell<real> c = make_cell<real>(m, m->cur);
     if (m->box.steps && box_takes<real>(c)) return Route::box;
     if (m->pair.vec && step2_takes<real>(c)) return Route::pairs;
@@ -854,7 +855,7 @@ extern "C" mrtlbm_status mrtlbm_autotune(mrtlbm_medium *m, const char *cache_pat
     Launch bestL = m->launch;
     double bestms = 1e300;
     const Launch saved = m->launch;
-    const bool saved_single = m->single;
+    const bool saved_single = m->single, saved_tuned = m->tuned_single;
     m->single = true;  // the shape is the single step's
     for (int vec : {4, 2, 1})
         for (int bx : {8, 16, 32, 64})
@@ -873,6 +874,7 @@ extern "C" mrtlbm_status mrtlbm_autotune(mrtlbm_medium *m, const char *cache_pat
                 if (st != MRTLBM_OK) {
                     m->launch = saved;
                     m->single = saved_single;
+                    m->tuned_single = saved_tuned;
                     drop_graphs(m);
                     return st;
                 }
@@ -882,7 +884,27 @@ extern "C" mrtlbm_status mrtlbm_autotune(mrtlbm_medium *m, const char *cache_pat
                 }
             }
     m->launch = bestL;
-    m->single = false;
+    // several steps per launch only where they beat the tuned single step (FP32
+    // moments 96^3: 7.2 us per step in pairs, 6.9 tuned)
+    m->single = m->tuned_single = false;
+    drop_graphs(m);
+    const Route r = m->prec == MRTLBM_F64 ? route<double>(m) : route<float>(m);
+    if (r != Route::single) {
+        double severalms = 1e300, ms = 0;
+        st = mrtlbm_time_steps(m, 2, &ms);  // warm-up
+        for (int i = 0; i < 3 && st == MRTLBM_OK; i++) {
+            st = mrtlbm_time_steps(m, n, &ms);
+            severalms = std::min(severalms, ms);
+        }
+        if (st != MRTLBM_OK) {
+            m->launch = saved;
+            m->single = saved_single;
+            m->tuned_single = saved_tuned;
+            drop_graphs(m);
+            return st;
+        }
+        m->tuned_single = bestms < severalms;
+    }
     drop_graphs(m);
     m->initialised = false;
     if (best) {
@@ -899,7 +921,7 @@ extern "C" mrtlbm_status mrtlbm_autotune(mrtlbm_medium *m, const char *cache_pat
         }
         std::ostringstream l;
         l << key << ' ' << bestL.vec << ' ' << bestL.bx << ' ' << bestL.by << ' ' << bestL.nt << ' ' << bestL.map << ' '
-          << (bestms / n);
+          << (bestms / n) << (m->tuned_single ? " single" : "");
         lines.push_back(l.str());
         std::ofstream o(cache_path, std::ios::trunc);
         for (auto &s : lines) o << s << '\n';
@@ -918,9 +940,13 @@ extern "C" mrtlbm_status mrtlbm_load_tuned(mrtlbm_medium *m, const char *cache_p
         std::istringstream r(line.substr(key.size() + 1));
         Launch L{};
         if (r >> L.vec >> L.bx >> L.by >> L.nt >> L.map && launch_ok(m, L)) {
+            double ms;
+            std::string every;  // "single": the shape serves every step
+            r >> ms >> every;
             drop_graphs(m);
             m->launch = L;
             m->single = false;
+            m->tuned_single = every == "single";
             return MRTLBM_OK;
         }
     }

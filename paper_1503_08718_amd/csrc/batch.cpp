@@ -398,7 +398,7 @@ extern "C" mrtlbm_status mrtlbm_batch_autotune(mrtlbm_medium *const *cells, int 
     mrtlbm_medium *m0 = cells[0];
     const int bx = std::min(bt, 64);
     m0->launch = Launch{bv, bx, bt / bx, bn, bm};
-    m0->single = false;
+    m0->single = m0->tuned_single = false;
     drop_graphs(m0);
     for (int i = 0; i < n; i++) {
         cells[i]->initialised = false;

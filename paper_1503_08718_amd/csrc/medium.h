@@ -74,6 +74,7 @@ struct mrtlbm_medium {
     mrt::Step2Shape pair, pop_pair;  // how two steps per pass are cut into blocks, per storage
     mrt::BoxShape box;         // small cells: several steps per launch
     bool single = false;       // every step its own launch, in the shape the caller set
+    bool tuned_single = false; // the same, as the tuned shape was faster (this cell alone, not in a batch)
     std::vector<mrt::GraphEntry> graphs;
 };
 

@@ -166,3 +166,32 @@ def test_failed_autotune_leaves_the_callers_shape():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, "-c", FAILED_AUTOTUNE], cwd=root, capture_output=True, text=True, timeout=100)
     assert "kept" in r.stdout, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("shape,prec,storage", [((96, 96, 96), "f32", "moments"), ((63, 64, 73), "f32", "moments"),
+                                                ((128, 128, 128), "f64", "moments"), ((16, 16, 16), "f64", "populations"),
+                                                ((20, 12, 9), "f32", "populations")], ids=ids)
+def test_autotune_keeps_the_faster_route(api, tmp_path, shape, prec, storage):
+    """After autotune the steps are not slower than in the shape that it
+    found (by more than the times vary); another medium that loads the file
+    takes the same kernel."""
+    g = _cell(api, shape, prec, storage, 0, (P, P, P))
+    launch = g.autotune(str(tmp_path / "tuned.txt"))
+    route = g.step_kernel()
+    h = _cell(api, shape, prec, storage, 0, (P, P, P))
+    assert h.load_tuned(str(tmp_path / "tuned.txt"))
+    assert h.step_kernel() == route and h.info()["launch"] == launch
+    g.init()
+    best = {}
+    for _ in range(4):
+        for name in ("tuned", "shape"):
+            if name == "tuned":
+                assert g.load_tuned(str(tmp_path / "tuned.txt"))
+            else:
+                g.set_launch(*launch)
+            g.time_steps(64)
+            best[name] = min(best.get(name, 1e9), g.time_steps(256))
+    assert best["tuned"] < 1.03 * best["shape"], best
+    old = (tmp_path / "tuned.txt").read_text().replace(" single", "")  # a file without the mark
+    (tmp_path / "old.txt").write_text(old)
+    assert h.load_tuned(str(tmp_path / "old.txt")) and h.info()["launch"] == launch
