@@ -85,12 +85,10 @@ Step2Shape pop2_shape(int nx, int ny, int nz, int nphase) {
         // FP32 120^3 took blocks of 6 and 20.3 us per step; single 17.5, blocks of 8 15.8)
         const int simd = sizeof(real) * vec > 16 ? 2 : 3;
         const int occ = std::min(waves > 4 ? simd / ((waves + 3) / 4) : 4 * simd / waves, (int)(POP2_LDS / lds));
-        int before = 0;
-        for (int planes = nz; planes >= 1; planes--) {
+        // each possible number of chunks, with the fewest planes that give it
+        for (int planes = nz, per; planes >= 1; planes = per - 1) {
             const int nchunks = (nz + planes - 1) / planes;
-            if (nchunks == before) continue;  // the fewest planes of each count
-            before = nchunks;
-            const int per = (nz + nchunks - 1) / nchunks;
+            per = (nz + nchunks - 1) / nchunks;
             const double t = pop2_model(sizeof(real), vec, (double)N, tr, waves, (long long)ntiles * nchunks, occ, per);
             if (t < tmin) {
                 tmin = t;

@@ -87,12 +87,10 @@ Step2Shape step2_shape(int nx, int ny, int nz, int nphase) {
         if (lds > (size_t)STEP2_LDS) continue;
         const int waves = (tr + 4 + rpw - 1) / rpw;
         const int occ = std::min(maxw / waves, (int)(STEP2_LDS / lds));
-        int before = 0;
-        for (int planes = nz; planes >= 1; planes--) {
+        // each possible number of chunks, with the fewest planes that give it
+        for (int planes = nz, per; planes >= 1; planes = per - 1) {
             const int nchunks = (nz + planes - 1) / planes;
-            if (nchunks == before) continue;  // the fewest planes of each count
-            before = nchunks;
-            const int per = (nz + nchunks - 1) / nchunks;
+            per = (nz + nchunks - 1) / nchunks;
             const double t = step2_model(per_wave, tr, rpw, (long long)ntiles * nchunks, occ, per);
             if (t < tmin) {
                 tmin = t;

@@ -195,3 +195,23 @@ def test_autotune_keeps_the_faster_route(api, tmp_path, shape, prec, storage):
     old = (tmp_path / "tuned.txt").read_text().replace(" single", "")  # a file without the mark
     (tmp_path / "old.txt").write_text(old)
     assert h.load_tuned(str(tmp_path / "old.txt")) and h.info()["launch"] == launch
+
+
+def test_long_cells_are_created_as_fast(api):
+    """The choice of a shape looks at each number of chunks once, not at each
+    number of planes: a cell of 60000 planes of 4 x 2 nodes takes about as
+    long to set up as one of 60 planes."""
+    import time
+
+    import torch
+
+    best = {}
+    for nz in (60, 60000, 60, 60000):
+        phase = torch.zeros((nz, 2, 4), dtype=torch.uint8, device="cuda")
+        for _ in range(20):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            g = api.Medium(phase, K[:1])
+            best[nz] = min(best.get(nz, 1e9), time.perf_counter() - t)
+            g.close()
+    assert best[60000] < 3 * best[60], best
