@@ -215,3 +215,32 @@ def test_long_cells_are_created_as_fast(api):
             best[nz] = min(best.get(nz, 1e9), time.perf_counter() - t)
             g.close()
     assert best[60000] < 3 * best[60], best
+
+
+def test_large_batches_lose_little_time_on_the_host(api):
+    """600 small cells that leave one by one, checked every 20 steps: choosing
+    the shape of two steps per pass again and again costs less than it
+    gains over single steps (which a caller-set block shape selects)."""
+    import time
+
+    import torch
+
+    rng = np.random.default_rng(5)
+    cells = []
+    for _ in range(600):
+        phase = rng.integers(0, 2, rng.integers(10, 20, 3)).astype(np.uint8)
+        k = np.array([[1.0, 1, 1, 0, 0, 0], [10.0 ** rng.uniform(0, 2)] * 3 + [0, 0, 0]])
+        cells.append(api.Medium(phase, k, precision="f32", storage="moments").set_bc(0))
+    launch = cells[0].info()["launch"]
+    best = {}
+    for _ in range(3):
+        for single in (True, False):
+            cells[0].set_launch(*launch) if single else cells[0].set_launch()
+            assert api.batch_step_kernel(cells)[0] == ("k_batch" if single else "k_batch2")
+            for c in cells:
+                c.init()
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            api.batch_solve(cells, tol=1e-3, kind="keff", max_steps=8000, check_every=20)
+            best[single] = min(best.get(single, 1e9), time.perf_counter() - t)
+    assert best[False] < 1.2 * best[True], best
