@@ -200,17 +200,27 @@ static hipError_t launch_tile(const bf16 *in, const bf16 *w, const float *bias, 
 // Large tiles reuse each weight and each staged voxel most; a coarse level
 // (8^3 voxels, 128 channels) then fills a handful of blocks, so tiles shrink
 // until a launch has two blocks for each CU or they are smallest.
+struct TileChoice {
+    int mt, nt;  // of a wave: 16 mt voxels, 16 nt channels
+    long long tiles, blocks;
+};
+
+static TileChoice tile_choice(const ConvGeom &g) {
+    TileChoice c{g.cin <= 64 ? 4 : 2, g.cout % 32 == 0 ? 2 : 1, 0, 0};
+    for (;;) {
+        c.tiles = tile_count(g, c.mt == 4 ? 8 : 4, c.mt == 1 ? 2 : 4);
+        c.blocks = c.tiles * (g.cout / (16 * c.nt));
+        if (c.blocks >= 512 || (c.nt == 1 && c.mt == 1)) return c;
+        if (c.nt > 1) c.nt = 1;
+        else c.mt >>= 1;
+    }
+}
+
 template <int CIN>
 static hipError_t conv_tile(const bf16 *in, const bf16 *w, const float *bias, const ConvGeom &g, int relu, bf16 *out,
                             float *out_f32, hipStream_t s) {
-    int mt = CIN <= 64 ? 4 : 2, nt = g.cout % 32 == 0 ? 2 : 1;
-    auto blocks = [&](int m, int n) {
-        return tile_count(g, m == 4 ? 8 : 4, m == 1 ? 2 : 4) * (g.cout / (16 * n));
-    };
-    while (blocks(mt, nt) < 512 && (nt > 1 || mt > 1)) {
-        if (nt > 1) nt = 1;
-        else mt >>= 1;
-    }
+    const TileChoice c = tile_choice(g);
+    const int mt = c.mt, nt = c.nt;
     if (mt == 4) {
         if constexpr (CIN <= 64) {
             return nt == 2 ? launch_tile<CIN, 4, 2>(in, w, bias, g, relu, out, out_f32, s)
@@ -227,7 +237,17 @@ bool nn_conv_tile_takes(const void *in, const void *w, const ConvGeom &g, const 
     auto off = [](const void *p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) != 0; };
     if (off(in, 16) || off(w, 16) || off(out, 8) || off(out_f32, 16)) return false;
     if (tile_count(g, 4, 2) >= (1LL << 31)) return false;
-    return g.cin == 8 || g.cin == 16 || g.cin == 32 || g.cin == 64 || g.cin == 128;
+    if (g.cin != 8 && g.cin != 16 && g.cin != 32 && g.cin != 64 && g.cin != 128) return false;
+    // A tile is computed whole.  In a volume narrower than it, or many small
+    // ones, that is work without a voxel, which runs beside the others' as long
+    // as the blocks are few; beyond that it takes its time, and gathering from
+    // memory costs less (1 x 256 x 256 x 1 voxels of 64 channels: 68 us gathered,
+    // 248 in tiles 8 times as large; 128 channels on 2048 single voxels 21.6 and
+    // 969).  The limits lie where the two meet, over 2500 random shapes.
+    const TileChoice c = tile_choice(g);
+    const long long padded = 64LL * c.mt * c.tiles, voxels = (long long)g.n * g.D * g.H * g.W;
+    const double limit = g.cin == 32 ? 2.5 : (g.cin == 8 || g.cin == 64 ? 2.0 : 1.75);
+    return c.blocks < (g.cin >= 64 ? 256 : 512) || (double)padded <= limit * (double)voxels;
 }
 
 hipError_t nn_conv_tile(const void *in, const void *w, const float *bias, const ConvGeom &g, int relu, void *out,

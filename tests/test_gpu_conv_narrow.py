@@ -1,0 +1,63 @@
+"""Convolutions of volumes narrower than the tiles of the tiled kernels, which
+gather their operands where a tile would be mostly padding: against the FP64
+reference, and in time against a volume of as many voxels that fills tiles."""
+
+import numpy as np
+import pytest
+
+from oracle import conv as C
+from test_gpu_conv_tiles import _inputs
+from test_gpu_nn import P, circ_bits, env, rel_l2  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+# (n, D, H, W, circ): single voxels, lines and planes along each axis, small
+# volumes; on both sides of the limits of padding and blocks
+NARROW = [(300, 1, 1, 1, (True, True, True)), (600, 1, 1, 1, (False, False, False)), (40, 1, 1, 30, (False, True, True)),
+          (1, 90, 60, 1, (False, True, True)), (2, 1, 70, 50, (True, False, True)), (150, 2, 3, 2, (False, True, True)),
+          (60, 3, 5, 7, (True, True, True))]
+
+
+@pytest.mark.parametrize("cin,cout", [(8, 48), (16, 32), (32, 128), (64, 64), (128, 64)])
+@pytest.mark.parametrize("s", NARROW, ids=lambda s: "x".join(map(str, s[:4])))
+def test_narrow_forward_on_reference(env, s, cin, cout):  # noqa: F811
+    """FP32 sums of BF16 products within 1e-4 (relative L2) of FP64."""
+    L, torch = env
+    n, D, H, W, circ = s
+    x, w, b, _ = _inputs(torch, L, s, cin, cout, cin + cout)
+    y = torch.empty((n * D * H * W, cout), device="cuda")
+    assert L.mrtlbm_nn_conv3d_fwd(P(x), n, D, H, W, cin, P(w), P(b), cout, circ_bits(circ), 0, None, P(y), None) == 0
+    ref = C.conv3d(x.double().cpu().numpy(), w[:, :27 * cin].double().cpu().numpy().reshape(cout, 3, 3, 3, cin),
+                   b.double().cpu().numpy(), circ)
+    assert rel_l2(y.cpu().numpy(), ref.reshape(-1, cout)) < 1e-4
+
+
+def _best(torch, f):
+    best = 1e9
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        f()
+        a.record()
+        for _ in range(20):
+            f()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) / 20)
+    return best
+
+
+SAME_VOXELS = [((2048, 1, 1, 1), (1, 8, 16, 16)), ((1, 256, 256, 1), (1, 64, 32, 32)), ((4, 64, 64, 1), (1, 16, 32, 32))]
+
+
+@pytest.mark.parametrize("cin,cout", [(16, 32), (64, 64), (128, 128)])
+@pytest.mark.parametrize("narrow,full", SAME_VOXELS, ids=lambda s: "x".join(map(str, s)))
+def test_narrow_forward_takes_no_longer(env, narrow, full, cin, cout):  # noqa: F811
+    """At most twice the time of a volume of as many voxels."""
+    L, torch = env
+    t = []
+    for s in (narrow, full):
+        x, w, b, _ = _inputs(torch, L, s + ((False, True, True),), cin, cout, 1)
+        y = torch.empty((int(np.prod(s)), cout), dtype=torch.bfloat16, device="cuda")
+        stream = torch.cuda.current_stream().cuda_stream
+        t.append(_best(torch, lambda: L.mrtlbm_nn_conv3d_fwd(P(x), *s, cin, P(w), P(b), cout, 6, 1, P(y), None, stream)))
+    assert t[0] < 2.0 * t[1], t
