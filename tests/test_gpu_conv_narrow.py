@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from oracle import conv as C
-from test_gpu_conv_tiles import _inputs
+from test_gpu_conv_tiles import _inputs, _wgrad
 from test_gpu_nn import P, circ_bits, env, rel_l2  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -30,6 +30,20 @@ def test_narrow_forward_on_reference(env, s, cin, cout):  # noqa: F811
     ref = C.conv3d(x.double().cpu().numpy(), w[:, :27 * cin].double().cpu().numpy().reshape(cout, 3, 3, 3, cin),
                    b.double().cpu().numpy(), circ)
     assert rel_l2(y.cpu().numpy(), ref.reshape(-1, cout)) < 1e-4
+
+
+@pytest.mark.parametrize("cin,cout", [(8, 48), (16, 32), (32, 128), (64, 64), (128, 64)])
+@pytest.mark.parametrize("s", NARROW, ids=lambda s: "x".join(map(str, s[:4])))
+def test_narrow_weight_gradient_on_reference(env, s, cin, cout):  # noqa: F811
+    """FP32 sums of BF16 products within 1e-4 (relative L2) of FP64."""
+    L, torch = env
+    x, _, _, dy = _inputs(torch, L, s, cin, cout, cin * cout)
+    dw, db = _wgrad(L, torch, s, cin, cout, x, dy, True)
+    _, rw, rb = C.conv3d_backward(x.double().cpu().numpy(), np.zeros((cout, 3, 3, 3, cin)), dy.double().cpu().numpy(),
+                                  s[4])
+    assert rel_l2(dw[:, :27 * cin].cpu().numpy(), rw.reshape(cout, 27 * cin)) < 1e-4
+    assert rel_l2(db.cpu().numpy(), rb) < 1e-4
+    assert not dw[:, 27 * cin:].any()
 
 
 def _best(torch, f):
@@ -61,3 +75,19 @@ def test_narrow_forward_takes_no_longer(env, narrow, full, cin, cout):  # noqa: 
         stream = torch.cuda.current_stream().cuda_stream
         t.append(_best(torch, lambda: L.mrtlbm_nn_conv3d_fwd(P(x), *s, cin, P(w), P(b), cout, 6, 1, P(y), None, stream)))
     assert t[0] < 2.0 * t[1], t
+
+
+@pytest.mark.parametrize("cin,cout", [(16, 32), (64, 64), (128, 128)])
+def test_narrow_weight_gradient_takes_no_longer(env, cin, cout):  # noqa: F811
+    """2048 single voxels: at most four times the time of one volume of as
+    many (three quarters of which is the fixed time of a launch or two)."""
+    L, torch = env
+    t = []
+    for s in ((2048, 1, 1, 1), (1, 8, 16, 16)):
+        x, _, _, dy = _inputs(torch, L, s + ((False, True, True),), cin, cout, 1)
+        scratch = torch.empty(L.mrtlbm_nn_wgrad_scratch_bytes(*s, cin, cout) // 4 + 4, device="cuda")
+        dw, db = torch.empty((cout, L.mrtlbm_nn_kpad(cin)), device="cuda"), torch.empty(cout, device="cuda")
+        stream = torch.cuda.current_stream().cuda_stream
+        t.append(_best(torch, lambda: L.mrtlbm_nn_conv3d_wgrad(P(x), P(dy), *s, cin, cout, 6, P(scratch), P(dw), P(db),
+                                                               stream)))
+    assert t[0] < 4.0 * t[1], t
