@@ -796,7 +796,8 @@ __global__ void k_to_temperature(const float *__restrict__ pred, int cpred, int 
 // for every voxel kept the address units busy.  64^3 to 128^3: 33.8 -> 13.9 us.
 constexpr int TEMP_X = 64, TEMP_Y = 4, TEMP_Z = 4, TEMP_LDS = 4096;
 
-__device__ __forceinline__ float coarse_at(int i, float r) { return ((float)i + 0.5f) * r - 0.5f; }
+// one operation for the range of a tile and for its voxels: they round alike
+__device__ __forceinline__ float coarse_at(int i, float r) { return fmaf((float)i + 0.5f, r, -0.5f); }
 
 __global__ void __launch_bounds__(256) k_to_temperature_tile(const float *__restrict__ pred, int cpred, int Dc, int Hc,
                                                              int Wc, int D, int H, int W, float scale, float margin,
@@ -1123,13 +1124,18 @@ hipError_t nn_to_temperature(const float *pred, int cpred, int Dc, int Hc, int W
                              float margin, float *T, int *bad, hipStream_t s) {
     const long long n = (long long)D * H * W;
     // a tile's coarse range has to fit: two values and one for every 1 / r
-    // voxels of each axis, one more for the rounding (any cell coarser than about
-    // three times finer than the grid does)
+    // voxels of each axis, one more for the rounding (whole tiles: the coarse grid is
+    // no finer than the cell)
     auto span = [](int tile, int fine, int coarse) {
         return (long long)std::ceil((double)std::min(tile, fine) * coarse / fine) + 3;
     };
     const long long range = span(TEMP_X, W, Wc) * span(TEMP_Y, H, Hc) * span(TEMP_Z, D, Dc);
-    if (n < (1LL << 31) && range <= TEMP_LDS)
+    // and its voxels are mostly there, in enough tiles: of a narrow cell's tiles few
+    // threads have a voxel (512 x 512 x 8: 57 us, 45 gathered, 100000 x 1 x 1 107 and
+    // 29), and a few tiles take 1.5 us longer for the staging (26 and 24.5; 400 random shapes)
+    const long long tiles = (long long)((W + TEMP_X - 1) / TEMP_X) * ((H + TEMP_Y - 1) / TEMP_Y) * ((D + TEMP_Z - 1) / TEMP_Z);
+    const bool filled = tiles >= 256 && 10 * n >= 4 * tiles * TEMP_X * TEMP_Y * TEMP_Z;
+    if (n < (1LL << 31) && range <= TEMP_LDS && filled)
         hipLaunchKernelGGL(k_to_temperature_tile, dim3(nn_temp_blocks(n)), dim3(256), 0, s, pred, cpred, Dc, Hc, Wc, D, H,
                            W, scale, margin, T, bad);
     else if (n < (1LL << 31))
