@@ -219,10 +219,12 @@ __global__ void __launch_bounds__(256) k_conv_fwd_c(const bf16 *__restrict__ in,
 }
 
 // weights of the adjoint convolution: wt[ci][flip(tap) * cout + co] = w[co][tap * cin + ci]
+// (idx: unsigned where their number stays below 2^31)
+template <typename idx>
 __global__ void k_weight_flip(const bf16 *__restrict__ w, int cin, int cout, int kpad, int kpad_t, bf16 *__restrict__ wt) {
-    const unsigned total = (unsigned)cin * (unsigned)kpad_t;
-    for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
-        const int ci = (int)(i / (unsigned)kpad_t), kt = (int)(i - (unsigned)ci * (unsigned)kpad_t);
+    const idx total = (idx)cin * (idx)kpad_t;
+    for (idx i = (idx)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (idx)gridDim.x * blockDim.x) {
+        const int ci = (int)(i / (idx)kpad_t), kt = (int)(i - (idx)ci * (idx)kpad_t);
         bf16 val = (bf16)0.0f;
         if (kt < 27 * cout) {
             const int tapt = kt / cout, co = kt % cout;
@@ -935,8 +937,12 @@ hipError_t nn_conv_fwd(const void *in, const void *w, const float *bias, const C
 }
 
 hipError_t nn_weight_flip(const void *w, int cin, int cout, int kpad, int kpad_t, void *wt, hipStream_t s) {
-    hipLaunchKernelGGL(k_weight_flip, dim3(g1((long long)cin * kpad_t)), dim3(256), 0, s, (const bf16 *)w, cin, cout,
-                       kpad, kpad_t, (bf16 *)wt);
+    const dim3 grid(g1((long long)cin * kpad_t)), block(256);
+    if ((long long)cin * kpad_t < (1LL << 31))
+        hipLaunchKernelGGL(k_weight_flip<unsigned>, grid, block, 0, s, (const bf16 *)w, cin, cout, kpad, kpad_t, (bf16 *)wt);
+    else
+        hipLaunchKernelGGL(k_weight_flip<long long>, grid, block, 0, s, (const bf16 *)w, cin, cout, kpad, kpad_t,
+                           (bf16 *)wt);
     return hipGetLastError();
 }
 

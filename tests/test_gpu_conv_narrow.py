@@ -91,3 +91,26 @@ def test_narrow_weight_gradient_takes_no_longer(env, cin, cout):  # noqa: F811
         t.append(_best(torch, lambda: L.mrtlbm_nn_conv3d_wgrad(P(x), P(dy), *s, cin, cout, 6, P(scratch), P(dw), P(db),
                                                                stream)))
     assert t[0] < 4.0 * t[1], t
+
+
+def test_input_gradient_of_more_weights_than_32_bits_count(env):  # noqa: F811
+    """12624 -> 12624 channels (4.3e9 weights, 8.6 GB) on one voxel with all
+    axes periodic, so that every tap and weight counts.  Whole numbers: the
+    FP32 sums are exact and the BF16 result is their rounding."""
+    L, torch = env
+    c = 12624
+    kpad = L.mrtlbm_nn_kpad(c)
+    assert c * kpad > 1 << 32
+    g = torch.Generator(device="cuda").manual_seed(1)
+    w = torch.zeros((c, kpad), dtype=torch.bfloat16, device="cuda")
+    dy = torch.randint(-1, 2, (c,), generator=g, device="cuda").to(torch.bfloat16)
+    ref = torch.zeros(c, device="cuda")
+    for t in range(27):
+        part = torch.randint(-1, 2, (c, c), generator=g, device="cuda", dtype=torch.int8).to(torch.bfloat16)
+        w[:, t * c:(t + 1) * c] = part
+        ref += dy.float() @ part.float()
+    wt = torch.full((c * kpad,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    dx = torch.empty(c, dtype=torch.bfloat16, device="cuda")
+    assert L.mrtlbm_nn_conv3d_dgrad(P(dy), 1, 1, 1, 1, c, P(w), c, 7, P(wt), P(dx), None) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(dx, ref.to(torch.bfloat16))
