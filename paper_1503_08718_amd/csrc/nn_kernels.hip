@@ -538,18 +538,19 @@ __global__ void k_up2_fwd(const bf16 *__restrict__ in, int n, int D, int H, int 
     }
 }
 
-// k_up2_fwd on 8 channels per thread (c8 = c / 8 groups per voxel, fewer than
-// 2^31 groups)
+// k_up2_fwd on 8 channels per thread (c8 = c / 8 groups per voxel; idx: unsigned
+// for fewer than 2^31 groups)
+template <typename idx>
 __global__ void k_up2_fwd8(const bf16x8 *__restrict__ in, int n, int D, int H, int W, int c8, bf16x8 *__restrict__ out) {
     const unsigned D2 = 2 * D, H2 = 2 * H, W2 = 2 * W;
-    const unsigned total = (unsigned)n * D2 * H2 * W2 * c8;
-    for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
-        unsigned r = i / c8;
-        const unsigned cg = i - r * c8, x = r % W2;
+    const idx total = (idx)n * D2 * H2 * W2 * c8;
+    for (idx i = (idx)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (idx)gridDim.x * blockDim.x) {
+        idx r = i / c8;
+        const idx cg = i - r * c8, x = r % W2;
         r /= W2;
-        const unsigned y = r % H2;
+        const idx y = r % H2;
         r /= H2;
-        const unsigned z = r % D2, nb = r / D2;
+        const idx z = r % D2, nb = r / D2;
         out[i] = in[(((nb * D + z / 2) * H + y / 2) * W + x / 2) * c8 + cg];
     }
 }
@@ -1060,12 +1061,15 @@ hipError_t nn_up2(int fwd, const void *in, int n, int D, int H, int W, int c, vo
     const long long small = (long long)n * D * H * W * c;
     if (groups8(in, out, small * 8, c)) {
         if (fwd)
-            hipLaunchKernelGGL(k_up2_fwd8, dim3(g1(small)), dim3(256), 0, s, (const bf16x8 *)in, n, D, H, W, c / 8,
-                               (bf16x8 *)out);
+            hipLaunchKernelGGL(k_up2_fwd8<unsigned>, dim3(g1(small)), dim3(256), 0, s, (const bf16x8 *)in, n, D, H, W,
+                               c / 8, (bf16x8 *)out);
         else
             hipLaunchKernelGGL(k_sum2_8, dim3(g1(small / 8)), dim3(256), 0, s, (const bf16x8 *)in, n, D, H, W, c / 8, 1.0f,
                                (bf16x8 *)out);
-    } else if (fwd)
+    } else if (fwd && c % 8 == 0 && aligned16(in) && aligned16(out))
+        hipLaunchKernelGGL(k_up2_fwd8<long long>, dim3(g1(small)), dim3(256), 0, s, (const bf16x8 *)in, n, D, H, W, c / 8,
+                           (bf16x8 *)out);
+    else if (fwd)
         hipLaunchKernelGGL(k_up2_fwd, dim3(g1(small * 8)), dim3(256), 0, s, (const bf16 *)in, n, D, H, W, c, (bf16 *)out);
     else
         hipLaunchKernelGGL(k_up2_bwd, dim3(g1(small)), dim3(256), 0, s, (const bf16 *)in, n, D, H, W, c, (bf16 *)out);

@@ -31,6 +31,20 @@ def test_pool_and_upsampling_equal_general_kernels(env, shape, forward):  # noqa
         assert torch.equal(got, ref[1:1 + size.numel()])
 
 
+def test_upsampling_beyond_32_bit_groups(env):  # noqa: F811
+    """2^31 groups of 8 channels (a 34 GB output): each takes its coarse voxel."""
+    L, torch = env
+    e, c = 512, 16
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randint(-128, 128, (e, e, e, c), generator=g, device="cuda", dtype=torch.int8).to(torch.bfloat16)
+    y = torch.empty((e, 2, e, 2, e, 2, c), dtype=torch.bfloat16, device="cuda")
+    assert y.numel() // 8 == 1 << 31
+    assert L.mrtlbm_nn_up2(1, P(x), 1, e, e, e, c, P(y), None) == 0
+    for z in range(0, e, 64):
+        for d in range(8):
+            assert torch.equal(y[z:z + 64, d >> 2, :, d >> 1 & 1, :, d & 1], x[z:z + 64]), (z, d)
+
+
 @pytest.mark.parametrize("coarse,fine", [((8, 8, 8), (16, 16, 16)), ((1, 2, 3), (5, 4, 7)), ((9, 21, 40), (19, 33, 130)),
                                          ((16, 16, 48), (9, 11, 65)), ((40, 40, 40), (7, 6, 9)),
                                          ((64, 64, 64), (128, 96, 72))], ids=str)
