@@ -236,7 +236,6 @@ static hipError_t conv_tile(const bf16 *in, const bf16 *w, const float *bias, co
 bool nn_conv_tile_takes(const void *in, const void *w, const ConvGeom &g, const void *out, const void *out_f32) {
     auto off = [](const void *p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) != 0; };
     if (off(in, 16) || off(w, 16) || off(out, 8) || off(out_f32, 16)) return false;
-    if (tile_count(g, 4, 2) >= (1LL << 31)) return false;
     if (g.cin != 8 && g.cin != 16 && g.cin != 32 && g.cin != 64 && g.cin != 128) return false;
     // A tile is computed whole.  In a volume narrower than it, or many small
     // ones, that is work without a voxel, which runs beside the others' as long
@@ -245,6 +244,7 @@ bool nn_conv_tile_takes(const void *in, const void *w, const ConvGeom &g, const 
     // 248 in tiles 8 times as large; 128 channels on 2048 single voxels 21.6 and
     // 969).  The limits lie where the two meet, over 2500 random shapes.
     const TileChoice c = tile_choice(g);
+    if (c.tiles >= (1LL << 24)) return false;  // a grid holds fewer than 2^32 threads
     const long long padded = 64LL * c.mt * c.tiles, voxels = (long long)g.n * g.D * g.H * g.W;
     const double limit = g.cin == 32 ? 2.5 : (g.cin == 8 || g.cin == 64 ? 2.0 : 1.75);
     return c.blocks < (g.cin >= 64 ? 256 : 512) || (double)padded <= limit * (double)voxels;
