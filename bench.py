@@ -57,13 +57,19 @@ def bytes_per_update(prec: str, storage: str) -> float:
 # HBM bytes per pass over memory from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE
 # (KiB per dispatch, mean over the dispatches), each scaled by the counter's
 # reading for a copy of known size (mrtlbm_stream_copy, 1 GiB); keyed by
-# workload, storage and steps per pass.  Drop an entry whenever its kernel changes.
+# workload, kernel and, for single steps, the launch shape (vec, bx, by, nt, map).
+# Drop an entry whenever its kernel or the rule for its blocks changes.
 MEASURED_TRAFFIC = {
-    ("braid256_f32", "moments", 1): 563_201_378,
-    ("braid256_f32", "moments", 2): 580_211_342,
-    ("braid256_f32", "populations", 1): 956_425_998,
-    ("braid256_f32", "populations", 2): 994_986_857,
+    ("braid256_f32", "k_step moments", (4, 64, 4, 2, 1)): 563_201_378,
+    ("braid256_f32", "k_step2", None): 580_211_342,
+    ("braid256_f32", "k_step populations", (4, 64, 2, 3, 0)): 956_425_998,
+    ("braid256_f32", "k_pop2", None): 1_000_488_346,
 }
+
+
+def measured_traffic(workload, storage, kernel, launch):
+    key = (f"k_step {storage}", tuple(launch.values())) if kernel == "k_step" else (kernel, None)
+    return MEASURED_TRAFFIC.get((workload,) + key)
 
 
 def parse():
@@ -202,14 +208,14 @@ def mode_throughput(args):
     ms = g.time_steps(kt_steps)
     kern_us = ms * 1e3 / kt_steps
     launch = dict(zip(("vec", "bx", "by", "nt", "map"), g.info()["launch"]))
-    # the medium takes two steps per pass over memory where that is faster; a
-    # launch shape set by the caller selects single steps
+    # the medium takes several steps per pass over memory where that is faster;
+    # a launch shape set by the caller selects single steps
+    kernel, per_pass = g.step_kernel()
     g.set_launch(*launch.values())
     single_us = g.time_steps(kt_steps) * 1e3 / kt_steps
-    per_pass = 2 if kern_us < 0.9 * single_us else 1
     bpl /= per_pass
     achieved = bpl * nodes / (kern_us * 1e-6) / 1e9
-    traffic = MEASURED_TRAFFIC.get((args.workload, args.storage, per_pass))
+    traffic = measured_traffic(args.workload, args.storage, kernel, launch)
     line = {
         "metric": "MLUPS (million lattice updates per second) of the fused collide+stream step, with % of HBM peak",
         "value": round(mlups, 1),
@@ -239,7 +245,7 @@ def mode_throughput(args):
             "frac": round(achieved / HBM_PEAK_GBS, 4),
             "traffic": traffic,
             "traffic_vs_algorithmic": None if traffic is None else round(traffic / (per_pass * bpl * nodes), 4),
-            "kernel": "k_step" if per_pass == 1 else ("k_step2" if args.storage == "moments" else "k_pop2"),
+            "kernel": kernel,
             "kernel_us": round(kern_us * per_pass, 3),
             "steps_per_launch": per_pass,
             "us_per_step": round(kern_us, 3),

@@ -24,6 +24,20 @@ def test_help_lists_the_modes():
         assert mode in p.stdout
 
 
+def test_measured_traffic_is_that_of_the_kernel_and_shape():
+    sys.path.insert(0, ROOT)
+    import bench
+
+    names = ("vec", "bx", "by", "nt", "map")
+    tuned, other = dict(zip(names, (4, 64, 4, 2, 1))), dict(zip(names, (4, 32, 8, 0, 0)))
+    assert bench.measured_traffic("braid256_f32", "moments", "k_step", tuned) == 563_201_378
+    assert bench.measured_traffic("braid256_f32", "moments", "k_step", other) is None
+    for launch in (tuned, other):
+        assert bench.measured_traffic("braid256_f32", "moments", "k_step2", launch) == 580_211_342
+    assert bench.measured_traffic("braid128_f32", "moments", "k_step2", tuned) is None
+    assert bench.measured_traffic("braid256_f32", "moments", "k_box", tuned) is None
+
+
 def test_network_flop_count():
     # the U-Net's convolutions at 64^3: level-0 layers carry sum C_in*C_out =
     # 8*16 + 16*16 + 32*16 + 16*16 + 16*16, level 1 (32^3) 16*32 + 32*32 +
