@@ -59,7 +59,7 @@ __device__ __forceinline__ void pop2_core(const Cell<real> &c, const Lane2 &L, c
         if (L.wxr) right = c.sgn[0] * s.f[1][VEC - 1];
     }
     const double h = (double)c.h[GA];
-    constexpr int H = VEC < 2 ? VEC : 2;
+    constexpr int H = 2;
 #pragma unroll
     for (int v0 = 0; v0 < VEC; v0 += H) {
 #pragma unroll
@@ -159,7 +159,7 @@ __device__ __forceinline__ void march2_pop(const Cell<real> &c, char *smem, int 
     // where the second step finds f3 and f4 (rows 1 .. rows, or a wall row itself)
     const int mid3 = ylo ? own + len : max(own - 2 * len, 0), mid4 = yhi ? own : min(rl + 1, tr + 1) * 2 * len + L.slot + len;
 
-    constexpr bool NL = (NT & 1) != 0, NS = (NT & 2) != 0;
+    constexpr bool NS = (NT & 2) != 0;
     auto plane_of = [&](int p) __attribute__((always_inline)) {
         if (c.per[2]) return (long long)(p < 0 ? p + nz : (p >= nz ? p - nz : p)) * plane;
         return (long long)min(max(p, 0), nz - 1) * plane;
@@ -173,13 +173,13 @@ __device__ __forceinline__ void march2_pop(const Cell<real> &c, char *smem, int 
         const long long pb = plane_of(p);
         const real *s = c.src + pb;
         const bool zlo = !c.per[2] && p == 0, zhi = !c.per[2] && p == nz - 1;
-        row_load<real, VEC, RAG, NL>(s, off, in.f[0]);
-        row_load<real, VEC, RAG, NL>(s + N, off, in.f[1]);
-        row_load<real, VEC, RAG, NL>(s + 2 * N, off, in.f[2]);
-        row_load<real, VEC, RAG, NL>(s + 3 * N, off3, in.f[3]);
-        row_load<real, VEC, RAG, NL>(s + 3 * N, off4, in.f[4]);
-        row_load<real, VEC, RAG, NL>(zlo ? s + 6 * N : c.src + 5 * N + plane_of(p - 1), off, in.f[5]);
-        row_load<real, VEC, RAG, NL>(zhi ? s + 5 * N : c.src + 6 * N + plane_of(p + 1), off, in.f[6]);
+        row_load<real, VEC, RAG>(s, off, in.f[0]);
+        row_load<real, VEC, RAG>(s + N, off, in.f[1]);
+        row_load<real, VEC, RAG>(s + 2 * N, off, in.f[2]);
+        row_load<real, VEC, RAG>(s + 3 * N, off3, in.f[3]);
+        row_load<real, VEC, RAG>(s + 3 * N, off4, in.f[4]);
+        row_load<real, VEC, RAG>(zlo ? s + 6 * N : c.src + 5 * N + plane_of(p - 1), off, in.f[5]);
+        row_load<real, VEC, RAG>(zhi ? s + 5 * N : c.src + 6 * N + plane_of(p + 1), off, in.f[6]);
         ph = row_phase<VEC>(c.phase + pb, noff);
     };
     auto settle_in = [&]() __attribute__((always_inline)) {

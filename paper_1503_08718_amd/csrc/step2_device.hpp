@@ -73,12 +73,12 @@ __device__ __forceinline__ T MRT_GLOBAL *uniform(T *base) {
     return p;
 }
 
-template <typename real, int VEC, bool RAG, bool NT>
+template <typename real, int VEC, bool RAG>
 __device__ __forceinline__ void row_load(const real *base, unsigned off, real *v) {
     typedef typename VecOf<real, VEC, RAG>::type vt;
     asm volatile("" : "+v"(off));  // extended to 64 bits by the load itself
     const vt MRT_GLOBAL *q = (const vt MRT_GLOBAL *)((const char MRT_GLOBAL *)uniform(base) + off);
-    const vt t = NT ? __builtin_nontemporal_load(q) : *q;
+    const vt t = *q;
 #pragma unroll
     for (int i = 0; i < VEC; i++) v[i] = t[i];
 }
@@ -197,7 +197,7 @@ __device__ __forceinline__ void step2_core(const Cell<real> &c, const Lane2 &L, 
         if (L.wxr) { rT = c.sgn[0] * Tc[VEC - 1]; rX = -c.sgn[0] * Xc[VEC - 1]; }
     }
     const real *lo = row + (L.wyl ? 0 : -2 * len), *hi = row + (L.wyh ? 0 : 2 * len);
-    constexpr int H = VEC < 2 ? VEC : 2;
+    constexpr int H = 2;
 #pragma unroll
     for (int v0 = 0; v0 < VEC; v0 += H) {
         real Tym[H], Yym[H], Typ[H], Yyp[H];
@@ -261,7 +261,7 @@ __host__ __device__ constexpr long long step2_lds_reals(int tr, int len, int nph
 // The block's tile: rows y0 .. y0 + rows - 1 and planes z0 .. z0 + nplanes - 1
 // of cell c.  tr: rows the LDS is laid out for (rows <= tr).  blockDim.x is a
 // multiple of 64 and holds tr + 4 rows of ceil(nx / VEC) lanes, rows whole
-// inside a wave.
+// inside a wave.  NT bit 1: non-temporal stores, as for the single step.
 template <typename real, int VEC, bool RAG, int NT, int GA>
 __device__ __forceinline__ void march2(const Cell<real> &c, real *smem, int tr, int y0, int rows, int z0,
                                        int nplanes) {
@@ -307,7 +307,7 @@ __device__ __forceinline__ void march2(const Cell<real> &c, real *smem, int tr, 
     const int buf = (tr + 4) * 2 * len;  // [input, intermediate][parity][tr + 4][T, Y][len]
     real *own = tab + (long long)c.nphase * TAB2 + rl * 2 * len + L.slot;
 
-    constexpr bool NL = (NT & 1) != 0, NS = (NT & 2) != 0;
+    constexpr bool NS = (NT & 2) != 0;
     // planes -2 .. nz + 1 (nz >= 2); beyond a wall: any plane, its values are not used
     auto plane_of = [&](int p) __attribute__((always_inline)) {
         if (c.per[2]) return (long long)(p < 0 ? p + nz : (p >= nz ? p - nz : p)) * plane;
@@ -329,16 +329,16 @@ __device__ __forceinline__ void march2(const Cell<real> &c, real *smem, int tr, 
     };
     auto load_tz = [&](int p, TZ<real, VEC> &v) __attribute__((always_inline)) {
         const real *s = c.src + plane_of(p);
-        row_load<real, VEC, RAG, NL>(s, off, v.T);
-        if (first_step) row_load<real, VEC, RAG, NL>(s + 3 * N, off, v.Z);
+        row_load<real, VEC, RAG>(s, off, v.T);
+        if (first_step) row_load<real, VEC, RAG>(s + 3 * N, off, v.Z);
         if (!c.per[2] && (p == -1 || p == nz)) fold_z(v, v);
     };
     auto load_xy = [&](int p) __attribute__((always_inline)) {
         const long long pb = plane_of(p);
         const real *s = c.src + pb;
-        row_load<real, VEC, RAG, NL>(s + 2 * N, off, Y);
+        row_load<real, VEC, RAG>(s + 2 * N, off, Y);
         if (first_step) {
-            row_load<real, VEC, RAG, NL>(s + N, off, X);
+            row_load<real, VEC, RAG>(s + N, off, X);
             ph = row_phase<VEC>(c.phase + pb, noff);
         }
     };
