@@ -108,14 +108,15 @@ __global__ void __launch_bounds__(256) k_step(Cell<real> c) {
 // 100 to 160 VGPRs bounds it (three or four waves per SIMD; capped at 128 VGPRs
 // it spills, 18.9 -> 21 us at 128^3 FP32, and with a third of the blocks it
 // takes 26).  A flux field needs none of the sums: 22.9 -> 16.2 us without
-// them and with 16-byte stores.
+// them and with 16-byte stores.  The table is staged before the planes: behind
+// the first plane's loads, with a test of that in the loop, thin cells of many
+// planes took longer (FP64 populations 4 x 2 x 60000 127.5 us, 110 like this; 128^3
+// FP64 populations 43.4 and 41.5).
 template <typename real, int VEC, int MODE, int ST>
 __global__ void __launch_bounds__(256) k_check(Cell<real> c, int zper, double *partials, real *qout, real qscale) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     real *tab = reinterpret_cast<real *>(smem_raw);
-    // the table is staged behind the first plane's loads
-    const TablePrefetch<real> tp = table_prefetch(c);
-    bool staged = false;
+    load_table(c, tab);
     const int tx = threadIdx.x, bx = blockDim.x;
     int xv = blockIdx.x * bx + tx;
     int y = blockIdx.y * blockDim.y + threadIdx.y;
@@ -126,11 +127,7 @@ __global__ void __launch_bounds__(256) k_check(Cell<real> c, int zper, double *p
     acc.zero();
     const int z0 = blockIdx.z * zper, z1 = min(c.nz, z0 + zper);
     const XLink xl = chunk_links<VEC>(c, xv, tx, bx);
-    for (int z = z0; z < z1; z++)
-        node_update<real, VEC, MODE, 0, ST>(c, tab, xv, y, z, active, xl, acc, qout, qscale, [&](const real *&) {
-            if (!staged) table_commit(c, tab, tp);
-            staged = true;
-        });
+    for (int z = z0; z < z1; z++) node_update<real, VEC, MODE, 0, ST>(c, tab, xv, y, z, active, xl, acc, qout, qscale);
     const long long b = ((long long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
     if constexpr (observes(MODE)) block_reduce_store(acc, partials + b * NRED);
 }

@@ -244,3 +244,21 @@ def test_large_batches_lose_little_time_on_the_host(api):
             api.batch_solve(cells, tol=1e-3, kind="keff", max_steps=8000, check_every=20)
             best[single] = min(best.get(single, 1e9), time.perf_counter() - t)
     assert best[False] < 1.2 * best[True], best
+
+
+def test_observables_of_thin_cells_take_no_longer(api):
+    """k_eff of 4 x 2 x 60000 nodes in FP64 populations: at most as long as in
+    moments, whose loads are as many (by more than the times vary)."""
+    import time
+
+    import torch
+
+    best = {}
+    media = {s: _cell(api, (4, 2, 60000), "f64", s, 0, (P, P, P)) for s in ("moments", "populations")}
+    for _ in range(60):
+        for s, g in media.items():
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            g.keff()
+            best[s] = min(best.get(s, 1e9), time.perf_counter() - t)
+    assert best["populations"] < 1.02 * best["moments"], best
