@@ -152,6 +152,10 @@ static bool layout(int nx, int ny, int nz, int nphase, mrtlbm_precision p, int v
     const size_t N = (size_t)nx * ny * nz;
     size_t o = 0;
     off[2] = o; o = align256(o + partial_capacity(nx, ny) * NRED * 8); // partials
+    // a gap: where the arrays of the state are 2^27 bytes long (256^3 in FP64), how
+    // their start lies to the memory channels decides (k_eff: 175 us here, 190
+    // without the gap, 168 to 192 with others)
+    o += 256;
     off[3] = o; o = align256(o + (size_t)nphase * TABW * rs);          // phase tables
     off[0] = o; o = align256(o + values * N * rs);                     // buffer A
     off[1] = o; o = align256(o + values * N * rs);                     // buffer B

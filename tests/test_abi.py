@@ -55,6 +55,18 @@ def test_workspace_bytes(lib):
     assert lib.mrtlbm_workspace_bytes_storage(4, 4, 4, 2, _lib.F32, 2) == 0
 
 
+@pytest.mark.parametrize("n,nphase", [(256, 3), (16, 2), (75, 256)])
+@pytest.mark.parametrize("size,prec", [(4, _lib.F32), (8, _lib.F64)])
+def test_workspace_layout(lib, n, nphase, size, prec):
+    # partial sums, 256 bytes, phase tables, two state buffers, each from a
+    # multiple of 256 bytes
+    up = lambda b: (b + 255) // 256 * 256  # noqa: E731
+    head = up((((n + 15) // 16) * n + 4096) * 10 * 8) + 256 + up(nphase * 12 * size)
+    for storage, values in ((0, 7), (1, 4)):
+        total = lib.mrtlbm_workspace_bytes_storage(n, n, n, nphase, prec, storage)
+        assert total == head + 2 * up(values * n ** 3 * size)
+
+
 def test_errors_before_any_device_work(lib):
     # argument checks that return before the library touches the device
     out = ctypes.c_void_p()
