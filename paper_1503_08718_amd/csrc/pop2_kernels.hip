@@ -72,11 +72,14 @@ Step2Shape pop2_shape(int nx, int ny, int nz, int nphase) {
     const double slope = (sizeof(real) == 4 ? 8.6 : 15.5) * (nx % 2 ? 1.3 : 1.0);
     const double single = 2.4 + slope * 1e-6 * (double)N;
     double tmin = 0.95 * 2.0 * single;
+    int before = 0;
     for (int w = 1; w <= maxw; w++) {
         int tr = std::min(w * rpw - 2, ny);
         if (tr < 1) continue;
         const int ntiles = (ny + tr - 1) / tr;
         tr = (ny + ntiles - 1) / ntiles;
+        if (tr == before) continue;  // as many rows from more waves
+        before = tr;
         const size_t lds = (size_t)pop2_lds_bytes(sizeof(real), tr, len, nphase);
         if (lds > (size_t)POP2_LDS) continue;
         const int waves = (tr + 2 + rpw - 1) / rpw;

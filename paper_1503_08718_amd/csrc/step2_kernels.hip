@@ -79,11 +79,14 @@ Step2Shape step2_shape(int nx, int ny, int nz, int nphase) {
     const int single_vec = nx % 4 == 0 ? 4 : (nx % 2 == 0 ? 2 : 1);
     const double slope = (sizeof(real) == 4 ? 5.5 : 9.0) * (single_vec == 1 ? 3.0 : 1.0);
     double tmin = 2.0 * (2.4 + slope * 1e-6 * (double)N);
+    int before = 0;
     for (int w = 1; w <= maxw; w++) {
         int tr = std::min(w * rpw - 4, ny);
         if (tr < 1) continue;
         const int ntiles = (ny + tr - 1) / tr;
         tr = (ny + ntiles - 1) / ntiles;
+        if (tr == before) continue;  // as many rows from more waves
+        before = tr;
         const size_t lds = sizeof(real) * (size_t)step2_lds_reals(tr, len, nphase);
         if (lds > (size_t)STEP2_LDS) continue;
         const int waves = (tr + 4 + rpw - 1) / rpw;
