@@ -487,9 +487,10 @@ extern "C" const char *mrtlbm_step_kernel(const mrtlbm_medium *m, int *steps) {
 template <typename real>
 hipError_t mrt::plain_steps(mrtlbm_medium *m, long long n, hipStream_t s, int *cur) {
     const Route r = route<real>(m);
-    if (r == Route::box && n > 1) {
-        long long launches = (n + m->box.steps - 1) / m->box.steps;
-        if ((launches ^ n) & 1) launches++;
+    // a few steps may need as many launches as there are steps: single ones then
+    long long launches = r == Route::box ? (n + m->box.steps - 1) / m->box.steps : n;
+    if ((launches ^ n) & 1) launches++;
+    if (launches < n) {
         for (long long i = 0; i < launches; i++) {
             const int steps = (int)((n + launches - 1 - i) / (launches - i));
             hipError_t e = launch_box<real>(make_cell<real>(m, *cur), m->box, steps, s);
