@@ -75,9 +75,17 @@ Step2Shape step2_shape(int nx, int ny, int nz, int nphase) {
     const int maxw = (sizeof(real) * vec > 16 ? 512 : 1024) / 64;
     const double per_wave = sizeof(real) == 8 && vec == 2 ? 0.48 : 0.84;
     // two single steps: 2.4 us each and 5.5 (FP32) or 9 (FP64) us per million
-    // nodes with vectors of 4 and 2 nodes, three times that with single nodes
+    // nodes with vectors of 4 and 2 nodes; with single nodes 1.7 times that and
+    // as much more as a row's last block is idle, up to three times (226 random
+    // cells of odd rows and under 300000 nodes, whose launches are of a block's
+    // length: at three times for all, 16 of them lost more than 3% by taking
+    // pairs, 57 x 509 x 4 in FP64 31%; so 4 do, 9% at most)
     const int single_vec = nx % 4 == 0 ? 4 : (nx % 2 == 0 ? 2 : 1);
-    const double slope = (sizeof(real) == 4 ? 5.5 : 9.0) * (single_vec == 1 ? 3.0 : 1.0);
+    double slope = sizeof(real) == 4 ? 5.5 : 9.0;
+    if (single_vec == 1) {
+        const int bx = nx > 32 ? 64 : (nx > 16 ? 32 : 16);
+        slope *= std::min(3.0, 1.7 * ((nx + bx - 1) / bx * bx) / nx);
+    }
     double tmin = 2.0 * (2.4 + slope * 1e-6 * (double)N);
     int before = 0;
     for (int w = 1; w <= maxw; w++) {

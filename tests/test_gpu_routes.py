@@ -128,6 +128,24 @@ def test_population_route_is_the_faster(api, shape):
     assert best[False] < 1.05 * best[True], best
 
 
+# small cells of odd rows: flat ones, whose launches are mostly blocks that
+# start and drain, and long ones, where pairs gain
+@pytest.mark.parametrize("shape,prec,kernel", [((57, 509, 4), "f64", "k_step"), ((157, 128, 5), "f64", "k_step"),
+                                               ((55, 224, 15), "f32", "k_step"), ((7, 17, 984), "f64", "k_step2"),
+                                               ((75, 26, 95), "f32", "k_step2")], ids=ids)
+def test_small_odd_rows_route_is_the_faster(api, shape, prec, kernel):
+    g = _cell(api, shape, prec, "moments", 0, (P, P, P))
+    assert g.step_kernel()[0] == kernel
+    launch = g.info()["launch"]
+    best = {}
+    for _ in range(4):
+        for single in (True, False):
+            g.set_launch(*launch) if single else g.set_launch()
+            g.time_steps(64)
+            best[single] = min(best.get(single, 1e9), g.time_steps(512))
+    assert best[False] < 1.05 * best[True], best
+
+
 FAILED_AUTOTUNE = """
 import ctypes
 import numpy as np, torch
