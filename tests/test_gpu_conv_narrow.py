@@ -66,15 +66,17 @@ SAME_VOXELS = [((2048, 1, 1, 1), (1, 8, 16, 16)), ((1, 256, 256, 1), (1, 64, 32,
 @pytest.mark.parametrize("cin,cout", [(16, 32), (64, 64), (128, 128)])
 @pytest.mark.parametrize("narrow,full", SAME_VOXELS, ids=lambda s: "x".join(map(str, s)))
 def test_narrow_forward_takes_no_longer(env, narrow, full, cin, cout):  # noqa: F811
-    """At most twice the time of a volume of as many voxels."""
+    """At most twice the time of a volume of as many voxels, or three quarters
+    of that of a volume that fills the same tiles (8 voxels along the last
+    axis): where gathering is the cheaper of the two, and no cheaper than that."""
     L, torch = env
     t = []
-    for s in (narrow, full):
+    for s in (narrow, full, narrow[:3] + (8,)):
         x, w, b, _ = _inputs(torch, L, s + ((False, True, True),), cin, cout, 1)
         y = torch.empty((int(np.prod(s)), cout), dtype=torch.bfloat16, device="cuda")
         stream = torch.cuda.current_stream().cuda_stream
         t.append(_best(torch, lambda: L.mrtlbm_nn_conv3d_fwd(P(x), *s, cin, P(w), P(b), cout, 6, 1, P(y), None, stream)))
-    assert t[0] < 2.0 * t[1], t
+    assert t[0] < max(2.0 * t[1], 0.75 * t[2]), t
 
 
 @pytest.mark.parametrize("cin,cout", [(16, 32), (64, 64), (128, 128)])
