@@ -480,16 +480,23 @@ extern "C" const char *mrtlbm_step_kernel(const mrtlbm_medium *m, int *steps) {
     return r == Route::box ? "k_box" : (r == Route::pairs ? "k_step2" : (r == Route::single ? "k_step" : "k_pop2"));
 }
 
-// n steps, in pairs or more per launch where the medium takes them, in as many
-// launches as n in parity: the buffers have then changed places as n single
-// steps would have them, which graphs rely on, the medium's own and a caller's
-// (they start from one buffer at every replay)
+// A graph starts from one buffer at every replay.  Once a caller has captured a
+// call on this medium, its steps leave the state where single steps would.
+static void note_capture(mrtlbm_medium *m) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (!m->captured && hipStreamIsCapturing(m->stream, &st) == hipSuccess) m->captured = st != hipStreamCaptureStatusNone;
+}
+
+// n steps, in pairs or more per launch where the medium takes them; parity: in as
+// many launches as n in parity, so that the buffers have changed places as n
+// single steps would have them, which graphs rely on, the medium's own and a
+// caller's (always so, 20 steps and a check of 256^3 FP32 took 1.32 ms; 1.22)
 template <typename real>
-hipError_t mrt::plain_steps(mrtlbm_medium *m, long long n, hipStream_t s, int *cur) {
+hipError_t mrt::plain_steps(mrtlbm_medium *m, long long n, bool parity, hipStream_t s, int *cur) {
     const Route r = route<real>(m);
     // a few steps may need as many launches as there are steps: single ones then
     long long launches = r == Route::box ? (n + m->box.steps - 1) / m->box.steps : n;
-    if ((launches ^ n) & 1) launches++;
+    if (parity && ((launches ^ n) & 1)) launches++;
     if (launches < n) {
         for (long long i = 0; i < launches; i++) {
             const int steps = (int)((n + launches - 1 - i) / (launches - i));
@@ -501,7 +508,7 @@ hipError_t mrt::plain_steps(mrtlbm_medium *m, long long n, hipStream_t s, int *c
         return hipSuccess;
     }
     if (r == Route::pairs || r == Route::population_pairs) {
-        const long long pairs = n / 4 * 2;
+        const long long pairs = parity ? n / 4 * 2 : n / 2;
         for (long long i = 0; i < pairs; i++) {
             const Cell<real> c = make_cell<real>(m, *cur);
             hipError_t e = r == Route::pairs ? launch_step2<real>(c, m->pair, s) : launch_pop2<real>(c, m->pop_pair, s);
@@ -517,8 +524,8 @@ hipError_t mrt::plain_steps(mrtlbm_medium *m, long long n, hipStream_t s, int *c
     }
     return hipSuccess;
 }
-template hipError_t mrt::plain_steps<float>(mrtlbm_medium *, long long, hipStream_t, int *);
-template hipError_t mrt::plain_steps<double>(mrtlbm_medium *, long long, hipStream_t, int *);
+template hipError_t mrt::plain_steps<float>(mrtlbm_medium *, long long, bool, hipStream_t, int *);
+template hipError_t mrt::plain_steps<double>(mrtlbm_medium *, long long, bool, hipStream_t, int *);
 
 template <typename real>
 static hipError_t check_step(mrtlbm_medium *m, int mode, hipStream_t s, int *cur, void *qout, double qscale) {
@@ -546,7 +553,7 @@ static mrtlbm_status get_graph(mrtlbm_medium *m, int K, bool with_check, hipGrap
     if (!m->cap_stream) HIPCHK(hipStreamCreateWithFlags(&m->cap_stream, hipStreamNonBlocking));
     HIPCHK(hipStreamBeginCapture(m->cap_stream, hipStreamCaptureModeThreadLocal));
     int cur = m->cur;
-    hipError_t e = plain_steps<real>(m, with_check ? K - 1 : K, m->cap_stream, &cur);
+    hipError_t e = plain_steps<real>(m, with_check ? K - 1 : K, true, m->cap_stream, &cur);
     if (e == hipSuccess && with_check) e = check_step<real>(m, 1, m->cap_stream, &cur, nullptr, 0.0);
     hipGraph_t graph = nullptr;
     hipError_t e2 = hipStreamEndCapture(m->cap_stream, &graph);
@@ -571,6 +578,7 @@ template <typename real>
 static mrtlbm_status do_steps(mrtlbm_medium *m, long long nsteps) {
     const int G = 64;
     long long done = 0;
+    note_capture(m);
     if (nsteps >= 2 * G) {
         hipGraphExec_t ge;
         mrtlbm_status st = get_graph<real>(m, G, false, &ge);
@@ -578,7 +586,7 @@ static mrtlbm_status do_steps(mrtlbm_medium *m, long long nsteps) {
         for (; done + G <= nsteps; done += G) HIPCHK(hipGraphLaunch(ge, m->stream));
     }
     int cur = m->cur;
-    HIPCHK(plain_steps<real>(m, nsteps - done, m->stream, &cur));
+    HIPCHK(plain_steps<real>(m, nsteps - done, m->captured, m->stream, &cur));
     m->cur = cur;
     m->steps += nsteps;
     return MRTLBM_OK;
@@ -595,6 +603,7 @@ extern "C" mrtlbm_status mrtlbm_init(mrtlbm_medium *m, const void *t0_dev, int f
     if (!m) return fail(MRTLBM_E_ARG, "medium is NULL");
     const double dT = m->t_hot - m->t_cold;
     hipError_t e;
+    note_capture(m);
     if (m->prec == MRTLBM_F64)
         e = launch_init<double>(make_cell<double>(m, 0), (double *)m->bufA, (const double *)t0_dev, flags, m->t_hot, dT,
                                 m->stream);
@@ -651,6 +660,7 @@ extern "C" mrtlbm_status mrtlbm_keff(mrtlbm_medium *m, mrtlbm_result *out) {
 extern "C" mrtlbm_status mrtlbm_flux(mrtlbm_medium *m, void *q_dev) {
     if (!m || !q_dev) return fail(MRTLBM_E_ARG, "NULL argument");
     if (!m->initialised) return fail(MRTLBM_E_ARG, "state not initialised");
+    note_capture(m);
     int cur = m->cur;
     hipError_t e = (m->prec == MRTLBM_F64) ? check_step<double>(m, 3, m->stream, &cur, q_dev, 1.0 / m->s)
                                            : check_step<float>(m, 3, m->stream, &cur, q_dev, 1.0 / m->s);
@@ -660,6 +670,7 @@ extern "C" mrtlbm_status mrtlbm_flux(mrtlbm_medium *m, void *q_dev) {
 extern "C" mrtlbm_status mrtlbm_temperature(mrtlbm_medium *m, void *t_dev) {
     if (!m || !t_dev) return fail(MRTLBM_E_ARG, "NULL argument");
     if (!m->initialised) return fail(MRTLBM_E_ARG, "state not initialised");
+    note_capture(m);
     const double dT = m->t_hot - m->t_cold;
     hipError_t e;
     if (m->prec == MRTLBM_F64)
@@ -739,7 +750,7 @@ static mrtlbm_status do_solve(mrtlbm_medium *m, double tol, mrtlbm_tol_kind kind
             m->steps += K;
         } else {
             int cur = m->cur;
-            HIPCHK(plain_steps<real>(m, left - 1, m->stream, &cur));
+            HIPCHK(plain_steps<real>(m, left - 1, m->captured, m->stream, &cur));
             HIPCHK(check_step<real>(m, 1, m->stream, &cur, nullptr, 0.0));
             m->cur = cur;
             m->steps += left;
@@ -798,6 +809,7 @@ extern "C" mrtlbm_status mrtlbm_set_storage(mrtlbm_medium *m, int storage) {
 extern "C" mrtlbm_status mrtlbm_state_get(mrtlbm_medium *m, void *f_dev) {
     if (!m || !f_dev) return fail(MRTLBM_E_ARG, "NULL argument");
     if (!m->initialised) return fail(MRTLBM_E_ARG, "state not initialised");
+    note_capture(m);
     const size_t bytes = (size_t)mrtlbm_state_values(m) * m->N * (m->prec == MRTLBM_F64 ? 8 : 4);
     HIPCHK(hipMemcpyAsync(f_dev, m->cur ? m->bufB : m->bufA, bytes, hipMemcpyDeviceToDevice, m->stream));
     return MRTLBM_OK;
@@ -806,6 +818,7 @@ extern "C" mrtlbm_status mrtlbm_state_get(mrtlbm_medium *m, void *f_dev) {
 extern "C" mrtlbm_status mrtlbm_state_set(mrtlbm_medium *m, const void *f_dev, long long steps) {
     if (!m || !f_dev) return fail(MRTLBM_E_ARG, "NULL argument");
     if (steps < 0) return fail(MRTLBM_E_ARG, "steps < 0");
+    note_capture(m);
     const size_t bytes = (size_t)mrtlbm_state_values(m) * m->N * (m->prec == MRTLBM_F64 ? 8 : 4);
     HIPCHK(hipMemcpyAsync(m->bufA, f_dev, bytes, hipMemcpyDeviceToDevice, m->stream));
     m->cur = 0;

@@ -75,6 +75,7 @@ struct mrtlbm_medium {
     mrt::BoxShape box;         // small cells: several steps per launch
     bool single = false;       // every step its own launch, in the shape the caller set
     bool tuned_single = false; // the same, as the tuned shape was faster (this cell alone, not in a batch)
+    bool captured = false;     // a caller captured a call: the buffers change places as by single steps from then on
     std::vector<mrt::GraphEntry> graphs;
 };
 
@@ -89,7 +90,7 @@ template <typename real>
 Cell<real> make_cell(const mrtlbm_medium *m, int cur);
 void drop_graphs(mrtlbm_medium *m);
 template <typename real>
-hipError_t plain_steps(mrtlbm_medium *m, long long n, hipStream_t s, int *cur);
+hipError_t plain_steps(mrtlbm_medium *m, long long n, bool parity, hipStream_t s, int *cur);
 void fill_result(const mrtlbm_medium *m, const double *f, mrtlbm_result *out);
 int stop_rule(StopState &ss, const mrtlbm_result &r, double tol, mrtlbm_tol_kind kind);
 bool has_side_flux(const mrtlbm_medium *m);

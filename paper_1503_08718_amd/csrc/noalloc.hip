@@ -73,7 +73,7 @@ static mrtlbm_status solve_noalloc(mrtlbm_medium *m, double tol, mrtlbm_tol_kind
         const long long left = max_steps - m->steps;
         const long long block = left >= K ? K : left;
         int cur = m->cur;
-        hipError_t e = plain_steps<real>(m, block - 1, m->stream, &cur);
+        hipError_t e = plain_steps<real>(m, block - 1, m->captured, m->stream, &cur);
         if (e != hipSuccess) return hip_fail(e, "step kernel");
         int nb = 0;
         e = launch_check<real>(make_cell<real>(m, cur), m->launch, 1, partials, &nb, nullptr, 0.0, m->stream);
