@@ -225,7 +225,8 @@ static double box_updates(int nx, int ty, int tz, int S) {
 // On top, what the boxes load beyond the 4 MB of those cells, at 3.7 TB/s, which
 // the overlapping halos need: a wider FP64 cell (88 x 64 x 16) took 8.8 with
 // (2, 2, 2), 3.7 of them for 20 MB, and is faster in single steps.  Counted from
-// the first byte, 16^3 FP64 got (3, 2, 2) and 1.82 us per step instead of 1.71.
+// the first byte, 16^3 FP64 got (3, 2, 2) and 1.82 us per step; so it takes
+// (3, 1, 2) and 1.71.
 // The model errs by a tenth, so a box has to promise that much.
 constexpr double BOX_T0 = 2.2, BOX_T1 = 0.7, BOX_T2 = 0.0009;
 

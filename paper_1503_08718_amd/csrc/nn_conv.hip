@@ -7,9 +7,9 @@
 // waves takes MT groups of 16 voxels of the tile and NT groups of 16 channels;
 // all read the same weights (L1) and their own voxels (LDS, one 16-byte read
 // per product, planes of 8 channels so that neighbouring lanes read
-// neighbouring 16 bytes).  Gathered from memory for each tap, as the kernel
-// this replaces did, the operands cost 27 reads of every activation through
-// L1, which bound it.  The products and their order (tap, then channel, in
+// neighbouring 16 bytes).  Gathered from memory for each tap, as k_conv_fwd does
+// (it still takes narrow volumes, other channel counts and alignments), the
+// operands cost 27 reads of every activation through L1, which bound it.  The products and their order (tap, then channel, in
 // chunks of 32) are those of k_conv_fwd: the results agree bit for bit.
 //
 // Gathered -> staged (MI355X): 16 -> 16 channels on 4 x 64^3 voxels 89 -> 40.7 us,

@@ -6,12 +6,19 @@
 // voxel.  A block stages a tile of dy and the same tile of x with its halo
 // once, as they are (planes of 16 channels), and reads every tap's operand
 // from there with the transposing LDS read (16 lanes take a 4 x 16 block and
-// each gets one column of it).  The kernel before staged a transposed copy of
-// the x columns for each tap, two bytes at a time: 27 gathers and 8 LDS writes
-// per 16 bytes.  16 -> 16 channels on 4 x 64^3 voxels: 317 -> 44 us, and 41 us
-// for the bias gradient of its own kernel -> none; 32 -> 16 there 355 -> 84;
-// 64 -> 64 on 4 x 16^3 38.6 -> 24.4; a training iteration 4.37 -> 2.02 ms.  LDS
-// reads bound it (two per product at 16 output channels).
+// each gets one column of it).  k_conv_wgrad_lds, which takes narrow volumes and
+// other channel counts, stages a transposed copy of the x columns for each tap,
+// two bytes at a time: 27 gathers and 8 LDS writes per 16 bytes.  The whole call
+// (kernel, bias gradient, sum of the partials), gathered -> staged: 16 -> 16
+// channels on 4 x 64^3 voxels 367 -> 56 us, 32 -> 16 there 638 -> 85, 64 -> 64 on
+// 4 x 16^3 74 -> 24; a training iteration 4.37 -> 2.02 ms.  LDS reads bound it
+// (two per product at 16 output channels).
+//
+// Partials and sums are FP32, in another order than the gathering kernel's.  Of
+// gradients that cancel (mean zero, 8 to 32 channels on 4 x 64^3 voxels) the
+// error against FP64 is 2.4e-7 to 2.7e-7 of their RMS where the gathering
+// kernel's is 1.6e-7 to 2.4e-7; on smaller volumes, coarser levels and
+// gradients of one sign it lies between four fifths and five fourths of it.
 //
 // A block owns CO output and CB input channels and all taps (the accumulators
 // of its waves; wave w takes the 16-column tiles w, w + 4, ...) and the tiles

@@ -2,9 +2,10 @@
 //
 // mrtlbm_solve replays hip graphs of K steps (graph instantiation allocates
 // host and device memory) and reduces the check-step observables in the
-// per-block partials of the medium's workspace.  This variant launches every
-// step on its own (no graph) and keeps the per-block partials and the final
-// reduction in `scratch`, a fixed device array of this file: a caller that
+// per-block partials of the medium's workspace.  This variant launches the same
+// kernels without a graph, one step or several per launch, and keeps the
+// per-block partials in `scratch`, a fixed device array of this file (the sums
+// go to the medium's pinned host memory): a caller that
 // cannot allocate (graph-free serving loops, harnesses that forbid it) only
 // has to have created the medium beforehand.  The kernels, their block
 // shapes and the reduction order are those of mrtlbm_solve, so both return
@@ -14,8 +15,7 @@
 // address returned by hipGetSymbolAddress, taken once per device with that
 // device current and kept in scratch_ptr[].  Every call on one device shares
 // that device's array; calls that overlap on one device race.  Nothing in it
-// has to start at zero: each check block writes its own slot of partials and
-// the reduction overwrites the final values.
+// has to start at zero: each check block writes its own slot of partials.
 #include <hip/hip_runtime.h>
 
 #include <mutex>

@@ -12,13 +12,17 @@
 //
 // The arithmetic of a node is that of the single-step kernels, operation by
 // operation and with the same random bits, so two single steps and one double
-// step agree bit for bit.  FP32 rounds all seven populations with a dither; that
-// (12 instructions each) is most of its arithmetic and bounds it: pairs are
-// faster only where single steps wait for memory.
+// step agree bit for bit.  FP32 rounds all seven populations with a dither (12
+// instructions each, 84 of 147 per node and step), and a block computes its
+// halo rows and end planes again: at 96^3, with rows of 24 lanes, two to a wave
+// of 64, that and the idle lanes make 1.85 times the arithmetic, and a block's
+// start and drain add 7 us (22.4 us a pair, 21.4 two single steps, which the
+// rule keeps there).
 //
-// Per step, single -> two per pass (MI355X): FP64 96^3 16.0 -> 11.9 us, 128^3 35.3
-// -> 21.9, 128 x 192 x 192 98.4 -> 53.9, 192^3 161 -> 88, 93 x 63 x 89 14.9 -> 8.5;
-// FP32 192^3 75.9 -> 54.8, 256^3 164 -> 124.
+// Per step, single -> two per pass (MI355X): FP64 96^3 16.8 -> 12.1 us, 128^3 35.4
+// -> 21.7, 128 x 192 x 192 98.0 -> 52.4, 192^3 162 -> 85, 93 x 63 x 89 15.2 -> 8.4;
+// FP32 120^3 17.4 -> 15.3, 128^3 20.0 -> 17.3, 192^3 75 -> 53, 256^3 164 -> 111,
+// 123 x 102 x 137 24.2 -> 15.7.
 #pragma once
 
 #include "step2_device.hpp"

@@ -1,8 +1,8 @@
 // Two time steps of moment storage in one pass over memory.
 //
 // The single-step kernel moves the whole state through memory once per step:
-// at 256^3 in FP32 it runs at the rate of a four-array copy, so only fewer
-// bytes can make it faster.  Here a block takes a tile of whole rows (all x,
+// at 256^3 in FP32 that is 5.75 TB/s, more than a copy of four arrays reaches
+// (5.12), so only fewer bytes can make it faster.  Here a block takes a tile of whole rows (all x,
 // `rows` rows in y) and marches through the planes of a z-chunk.  At plane p
 // it applies the first step to its rows and to one halo row on either side,
 // keeps the result on chip, and applies the second step to plane p - 1, whose
@@ -18,9 +18,10 @@
 // Per step, single -> two per pass (MI355X): FP32 256^3 95.6 -> 55.2 us, 192^3
 // 39.2 -> 25.6, 128^3 12.9 -> 10.5, 75 x 61 x 87 8.8 -> 5.6; FP64 256^3 195.5 ->
 // 106.6, 128^3 21.6 -> 13.4; batches in FP32, 24 solves of 64..128 per axis
-// 136 -> 84, 32 of 32..64 29.8 -> 22.0, 9 unit cells of 56 x 56 28.7 -> 18.2.  What bounds it now is the arithmetic (57 vector
-// instructions per node and step, 63 of 110 us at 256^3) together with the
-// 553 MB that two steps still move (5.0 TB/s; a four-array copy reaches 5.1).
+// 136 -> 84, 32 of 32..64 29.8 -> 22.0, 9 unit cells of 56 x 56 28.7 -> 18.2.
+// What bounds it now is the arithmetic (57 vector instructions per node and
+// step, 63 of 110 us at 256^3) together with the 580 MB that two steps still
+// move (measured, 5.26 TB/s; 553 MB without the halo rows read again).
 // Registers decide the layout: the planes of a vector of 4 leave 128 per wave
 // only if each value is dropped as soon as its last use is past (see settle);
 // with 140 a few spilled values made every prefetch wait, 98 us per step.

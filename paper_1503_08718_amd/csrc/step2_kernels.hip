@@ -79,7 +79,7 @@ Step2Shape step2_shape(int nx, int ny, int nz, int nphase) {
     // as much more as a row's last block is idle, up to three times (226 random
     // cells of odd rows and under 300000 nodes, whose launches are of a block's
     // length: at three times for all, 16 of them lost more than 3% by taking
-    // pairs, 57 x 509 x 4 in FP64 31%; so 4 do, 9% at most)
+    // pairs, 57 x 509 x 4 in FP64 31%; so 4 do, by 11% at most)
     const int single_vec = nx % 4 == 0 ? 4 : (nx % 2 == 0 ? 2 : 1);
     double slope = sizeof(real) == 4 ? 5.5 : 9.0;
     if (single_vec == 1) {
